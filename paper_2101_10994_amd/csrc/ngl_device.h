@@ -139,12 +139,11 @@ __device__ inline void descend(const ngl_model& md, int cx, int cy, int cz, int 
       if (alive) {
         const int s = depth - 1 - d;
         const int c = ((cx >> s) & 1) | ((cy >> s) & 1) << 1 | ((cz >> s) & 1) << 2;
+        // both words are requested together: one dependent read per depth
         const uint32_t mask = md.child_mask[d][v];
-        if (mask >> c & 1u) {
-          v = md.first_child[d][v] + __popc(mask & ((1u << c) - 1u));
-        } else {
-          alive = false;
-        }
+        const int child0 = md.first_child[d][v];
+        alive = (mask >> c & 1u) != 0;
+        v = alive ? child0 + __popc(mask & ((1u << c) - 1u)) : 0;
       }
       const int cur = alive ? v : -1;
       if (d >= 1) vox[d - 1] = cur;

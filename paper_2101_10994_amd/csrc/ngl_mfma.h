@@ -577,6 +577,92 @@ struct TileShape {
   static constexpr int D = M / 4;  // feature elements per lane
 };
 
+// A pointer to device memory that is the same in every lane, held as a
+// scalar (a model view read from LDS would otherwise give vector addresses).
+template <typename P>
+using gptr = const __attribute__((address_space(1))) P*;
+template <typename P>
+__device__ __forceinline__ gptr<P> uniform_ptr(const void* p) {
+  const uint64_t u = reinterpret_cast<uint64_t>(p);
+  const uint32_t lo = __builtin_amdgcn_readfirstlane(uint32_t(u)), hi = __builtin_amdgcn_readfirstlane(uint32_t(u >> 32));
+  return (gptr<P>)(uint64_t(hi) << 32 | lo);
+}
+
+// Tile-wise cooperative gather: the wavefront gathers and decodes its 64
+// points one 16-point tile at a time, the 4 lanes of group r = lane / 4
+// serving point r of the tile.  A corner row is read by the group in pieces
+// of 4 * EPL elements, lane g = lane % 4 taking EPL of them, so one load of
+// the group covers consecutive bytes (64 where the row is that wide).
+template <int M, typename FT>
+struct TileRows {
+  static constexpr int ES = std::is_same<FT, F32>::value ? 4 : 2;
+  static constexpr int D = M / 4;                             // feature elements per lane
+  static constexpr int EPL = D * ES >= 16 ? 16 / ES : D;      // of them consecutive, in one load
+  static constexpr int NLD = D / EPL;                         // loads per row and lane
+  static constexpr int W = EPL * ES / 4;                      // 32-bit words per load
+  typedef uint32_t Words __attribute__((ext_vector_type(W)));
+  // four corners' slices, as stored
+  struct Half {
+    Words v[4][NLD];
+  };
+  __device__ static uint32_t offset(int c, int g) { return uint32_t(c) * uint32_t(M * ES) + uint32_t(g * EPL * ES); }
+  __device__ static void issue(Half& h, gptr<char> base, const int4 c, int g) {
+    const int cs[4] = {c.x, c.y, c.z, c.w};
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const gptr<char> r = base + offset(cs[j], g);
+#pragma unroll
+      for (int q = 0; q < NLD; ++q) h.v[j][q] = *(gptr<Words>)(r + q * 4 * EPL * ES);
+    }
+  }
+  // from the LDS copy of level 1 (read as LDS, not through a generic address)
+  __device__ static void issue_lds(Half& h, const void* base, const int4 c, int g) {
+    typedef const __attribute__((address_space(3))) char* lptr;
+    const int cs[4] = {c.x, c.y, c.z, c.w};
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const lptr r = (lptr)(base) + offset(cs[j], g);
+#pragma unroll
+      for (int q = 0; q < NLD; ++q) h.v[j][q] = *(const __attribute__((address_space(3))) Words*)(r + q * 4 * EPL * ES);
+    }
+  }
+  // acc += w[j] * slice of corner j, corner by corner
+  __device__ static void add(const Half& h, const float* w, float* acc) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int q = 0; q < NLD; ++q)
+#pragma unroll
+        for (int e = 0; e < W; ++e) {
+          const uint32_t b = h.v[j][q][e];
+          if constexpr (ES == 4) {
+            acc[q * EPL + e] = fmaf(w[j], __uint_as_float(b), acc[q * EPL + e]);
+          } else {
+            const int i = q * EPL + 2 * e;
+            const float lo = std::is_same<FT, BF16>::value ? bf16_to_f32(b & 0xffffu) : f16_to_f32(b & 0xffffu);
+            const float hi = std::is_same<FT, BF16>::value ? bf16_to_f32(b >> 16) : f16_to_f32(b >> 16);
+            acc[i] = fmaf(w[j], lo, acc[i]);
+            acc[i + 1] = fmaf(w[j], hi, acc[i + 1]);
+          }
+        }
+  }
+  // the lane's accumulators into staging row r
+  template <class DEC>
+  __device__ static void put(typename DEC::Stage* rows, int r, int g, const float* acc) {
+#pragma unroll
+    for (int q = 0; q < NLD; ++q) DEC::template tile_slice<EPL>(rows, r, (4 * q + g) * EPL, acc + q * EPL);
+  }
+};
+
+// LDS per wavefront of a tile evaluation over up to `levels` levels: the
+// 16 staging rows, or before them the corner ids of the tile's points
+// ([16][levels][8], rows padded by 16 bytes to spread the banks).
+template <class DEC>
+__host__ __device__ constexpr int tile_lds_bytes(int levels) {
+  const int ids = 16 * 16 * (2 * levels + 1);
+  return ids > DEC::TILE_BYTES ? ids : DEC::TILE_BYTES;
+}
+
 // Level 1 (resolution 4, at most 5^3 corners) can be staged in LDS by the
 // block: its corner rows are then read through the LDS, off the vector
 // memory path that the other levels' rows load through.  Used with FP32
@@ -661,5 +747,198 @@ __device__ __forceinline__ void tile_level(const ngl_model& md, int l, int vq, c
 #pragma unroll
   for (int i = 0; i < D; ++i) acc[i] = vq >= 0 ? t[i] : acc[i];
 }
+
+// Trilinear weights of the eight corners for the point xq in the cell c of
+// level l (cell_local and corner_weight with a level known at run time: the
+// cell size is a power of two, formed from its exponent).
+__device__ __forceinline__ void level_weights(int l, uint32_t c, const float xq[3], float* w) {
+  const float step = __uint_as_float(uint32_t(127 - l) << 23);
+  const float half_r = __uint_as_float(uint32_t(127 + l) << 23);
+  const int ci[3] = {cell_x(c), cell_y(c), cell_z(c)};
+  float u[3];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    const float lo = -1.0f + float(ci[a]) * step;
+    u[a] = fminf(fmaxf((xq[a] - lo) * half_r, 0.0f), 1.0f);
+  }
+#pragma unroll
+  for (int j = 0; j < 8; ++j) w[j] = corner_weight(u, j);
+}
+
+// Packed cell at level l of the ancestor of the level-Lc cell c.
+__device__ __forceinline__ uint32_t cell_at(uint32_t c, int Lc, int l) {
+  const int sh = Lc - l;
+  return pack_cell(cell_x(c) >> sh, cell_y(c) >> sh, cell_z(c) >> sh);
+}
+
+// Points may be taken in another order than the lanes': `rank` is this
+// lane's place and `from` the lane whose point has this lane's place.
+struct PointOrder {
+  int rank, from;
+};
+
+// One SDF evaluation of the wavefront's 64 points: the features of levels
+// 1..lod summed, decoder lod, and for the points with `mix` the Eq. 3 blend
+// (weight a) with decoder lod + 1 on the sum with level lod + 1.  Each lane
+// brings its point: position x, voxel per level (-1: absent, then so are the
+// finer ones), the packed cell at level Lc, and `ok`, whether its result is
+// used.  Every lane of the wavefront must call it.
+//
+// The tiles with a used point are taken in turn.  A tile's corner ids are
+// read by the group, two per lane, for all levels at once and while the
+// tile before is decoded, and pass through LDS to the four lanes.  The rows
+// then stream through two register sets of four corners each: as soon as a
+// set is added, the same corners of the next level are requested into it,
+// so at least half a level's rows are always in flight and a tile waits for
+// one dependent read (ids, then rows) instead of two per level.  Used for
+// queries over 16-bit features (2^22 blended queries of the 7-LOD model 0.766
+// -> 0.701 ms); with FP32 features the two sets take the kernel from three
+// wavefronts per SIMD to two or make it spill (2^20 queries 0.209 -> 0.228 and
+// 0.235 ms), and in the normal kernel it measured the same.  Levels that
+// none of the tile's points has are skipped.  Every element is accumulated
+// over the corners and levels in the order of interp_level.
+//
+// SEL: points may lack a level that their tile runs (queries); they load
+// voxel 0's rows there and keep their accumulator.  Without SEL the results
+// of such lanes are unused.
+template <int M, typename FT, class DEC, bool SEL, bool ORDERED>
+__device__ __forceinline__ float tile_eval(const ngl_model& md, const DecLds<DEC>& S, const float x[3], const int* vox,
+                                           uint32_t cell, bool ok, bool mix, float a, int lod, int Lc, float b2a,
+                                           float b2b, const void* l1s, bool l1,
+                                           PointOrder order = PointOrder{}) {
+  using T = TileRows<M, FT>;
+  constexpr int D = T::D;
+  const int lane = threadIdx.x & 63, r = lane >> 2, g = lane & 3;
+  const int H = md.hidden;
+  typename DEC::Stage* rows = S.stage;
+  int32_t* ids = reinterpret_cast<int32_t*>(S.stage);
+  uint64_t okm = __ballot(ok), mixm = __ballot(mix);
+  if (ORDERED) {
+    // by place: the used points come first, and all of them blend or none
+    okm = __popcll(okm) == 64 ? ~0ull : (1ull << __popcll(okm)) - 1ull;
+    mixm = mixm ? okm : 0ull;
+    if (mixm) a = __shfl(a, order.from, 64);
+    mix = (mixm >> lane) & 1ull;
+  }
+  float mine = 0.0f;
+  if (okm == 0) return mine;
+  int2 idr[NGL_MAX_LODS];  // this lane's two corner ids per level of the next tile
+  int next_n = 0;          // levels that tile runs
+  uint32_t next_have = 0;  // SEL: bit l set when the group's point has level l
+  auto fetch = [&](int t) {
+    const int q = ORDERED ? __shfl(order.from, 16 * t + r, 64) : 16 * t + r;
+    const int top = ((mixm >> (16 * t)) & 0xffffull) ? lod + 1 : lod;
+    next_n = 0;
+    next_have = 0;
+#pragma unroll
+    for (int l = 1; l <= NGL_MAX_LODS; ++l) {
+      if (l > top) break;
+      const int vq = __shfl((ORDERED || l <= lod ? ok : mix) ? vox[l - 1] : -1, q, 64);
+      if (SEL) {
+        if (__ballot(vq >= 0) == 0) break;
+        next_have |= uint32_t(vq >= 0) << l;
+      }
+      next_n = l;
+      typedef int32_t i32x2 __attribute__((ext_vector_type(2)));
+      const i32x2 c = *(gptr<i32x2>)(uniform_ptr<int32_t>(md.corners[l - 1]) + size_t(vq >= 0 ? vq : 0) * 8 + 2 * g);
+      idr[l - 1] = make_int2(c[0], c[1]);
+    }
+  };
+  int t = (__ffsll((unsigned long long)okm) - 1) >> 4;
+  fetch(t);
+  for (;;) {
+    const int q = ORDERED ? __shfl(order.from, 16 * t + r, 64) : 16 * t + r;
+    const int n = next_n;
+    const uint32_t have = next_have;
+    const bool mt = ((mixm >> (16 * t)) & 0xffffull) != 0;
+    float xq[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) xq[k] = __shfl(x[k], q, 64);
+    const uint32_t cq = uint32_t(__shfl(int(cell), q, 64));
+    // the tile's corner ids through LDS
+    int32_t* idp = ids + r * 4 * (2 * n + 1);
+#pragma unroll
+    for (int l = 1; l <= NGL_MAX_LODS; ++l) {
+      if (l > n) break;
+      *reinterpret_cast<int2*>(idp + (l - 1) * 8 + 2 * g) = idr[l - 1];
+    }
+    wave_lds_sync();
+    float acc[D];
+#pragma unroll
+    for (int i = 0; i < D; ++i) acc[i] = 0.0f;
+    typename T::Half A, B;
+    auto corner_ids = [&](int l, int4& c0, int4& c1) {
+      const int4* p = reinterpret_cast<const int4*>(idp + (l - 1) * 8);
+      c0 = p[0];
+      c1 = p[1];
+    };
+    // acc += set h of level l (weights w), where the point has the level
+    auto add = [&](const typename T::Half& h, const float* w, int l) {
+      if (!SEL || ((have >> l) & 1u)) T::add(h, w, acc);
+    };
+    auto finish = [&](int l) {  // the pending rows of level l
+      float w[8];
+      level_weights(l, cell_at(cq, Lc, l), xq, w);
+      add(A, w, l);
+      add(B, w + 4, l);
+    };
+    const int l0 = l1_bytes<M, FT>() > 0 && l1 ? 2 : 1;  // first level read from memory
+    if (n >= l0) {
+      int4 c0, c1;
+      corner_ids(l0, c0, c1);
+      const gptr<char> feat = uniform_ptr<char>(md.feat[l0 - 1]);
+      T::issue(A, feat, c0, g);
+      T::issue(B, feat, c1, g);
+    }
+    if (l1_bytes<M, FT>() > 0 && l0 == 2 && n >= 1) {
+      int4 c0, c1;
+      corner_ids(1, c0, c1);
+      float w[8];
+      level_weights(1, cell_at(cq, Lc, 1), xq, w);
+      typename T::Half h;
+      T::issue_lds(h, l1s, c0, g);
+      add(h, w, 1);
+      T::issue_lds(h, l1s, c1, g);
+      add(h, w + 4, 1);
+    }
+#pragma unroll 1
+    for (int l = l0; l < n; ++l) {
+      int4 c0, c1;
+      corner_ids(l + 1, c0, c1);
+      const gptr<char> feat = uniform_ptr<char>(md.feat[l]);
+      float w[8];
+      level_weights(l, cell_at(cq, Lc, l), xq, w);
+      add(A, w, l);
+      T::issue(A, feat, c0, g);
+      add(B, w + 4, l);
+      T::issue(B, feat, c1, g);
+    }
+    // level n is pending; it belongs to decoder lod unless it is level lod + 1
+    const bool pend = n > lod;
+    if (!pend && n >= l0) finish(n);
+    wave_lds_sync();  // the ids are read; the staging rows take their place
+    T::template put<DEC>(rows, r, g, acc);
+    if (g == 0) DEC::tile_rest(rows, r, xq);
+    if (pend) finish(n);  // z_{L+1} = z_L + psi_{L+1}
+    const uint64_t later = t < 3 ? okm >> (16 * t + 16) : 0ull;
+    const int nt = later ? t + 1 + ((__ffsll((unsigned long long)later) - 1) >> 4) : 4;
+    if (nt < 4) fetch(nt);
+    wave_lds_sync();
+    float d = b2a + DEC::tile(S.frag0, S.w2s0, rows, H);
+    if (mt) {
+      wave_lds_sync();
+      T::template put<DEC>(rows, r, g, acc);
+      wave_lds_sync();
+      const float d1 = b2b + DEC::tile(S.frag1, S.w2s1, rows, H);
+      if (mix) d = (1.0f - a) * d + a * d1;
+    }
+    wave_lds_sync();
+    if ((lane >> 4) == t) mine = d;  // lane 16 t + j owns point 16 t + j
+    if (nt >= 4) break;
+    t = nt;
+  }
+  return ORDERED ? __shfl(mine, order.rank, 64) : mine;
+}
+
 
 }  // namespace ngl

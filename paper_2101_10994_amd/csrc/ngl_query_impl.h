@@ -173,21 +173,51 @@ __global__ __launch_bounds__(64 * NW) void k_query_mfma(ngl_model md, const floa
 // 1..lod, the decoder lod, and with `blend` the Eq. 3 mix (weight a, this
 // lane's) with decoder lod+1 on z + the level lod+1 voxel vn.  rows: this
 // wavefront's 16 staging rows.  Every lane must call it.
-template <int M, typename FT, class DEC>
+//
+// Points may be taken in another order than the lanes': with `order` set,
+// order.rank is this lane's place and order.from the lane whose point has
+// this lane's place.  Levels that no point of a tile has are skipped.
+// Order by how many levels a point has (voxels nest, so these are the
+// coarsest ones), most first, so that points in empty space share tiles
+// that skip the fine levels; lanes without a point come last.  2^20 FP32
+// queries, half of them uniform in the box (they have 2.7 of 5 levels on
+// average): 0.209 -> 0.193 ms; 2^22 blended queries of the 7-LOD 16-bit model
+// 0.829 -> 0.766 ms.
+__device__ __forceinline__ PointOrder order_by_depth(const int* vox, int Lp, bool act) {
+  const int lane = threadIdx.x & 63;
+  const uint64_t below = (1ull << lane) - 1ull;
+  int depth = 0;
+#pragma unroll
+  for (int l = 1; l <= NGL_MAX_LODS; ++l) depth += l <= Lp && vox[l - 1] >= 0;
+  if (!act) depth = -1;
+  int base = 0, rank = 0;
+#pragma unroll
+  for (int d = NGL_MAX_LODS; d >= -1; --d) {
+    if (d > Lp) continue;
+    const uint64_t m = __ballot(depth == d);
+    if (depth == d) rank = base + __popcll(m & below);
+    base += __popcll(m);
+  }
+  return {rank, __builtin_amdgcn_ds_permute(4 * rank, lane)};
+}
+
+template <int M, typename FT, class DEC, bool ORDERED>
 __device__ __forceinline__ float coop_eval(const ngl_model& md, const DecLds<DEC>& S, const float x[3],
                                            const int* vox, int cx, int cy, int cz, int vn, bool act, int lod, int Lp,
                                            bool blend, float a, float b2a, float b2b, const void* l1s = nullptr,
-                                           bool l1 = false) {
-  const uint64_t live = __ballot(act);  // tiles without an active point are skipped
+                                           bool l1 = false, PointOrder order = PointOrder{}) {
+  uint64_t live = __ballot(act);  // tiles without an active point are skipped
+  if (ORDERED) live = __popcll(live) == 64 ? ~0ull : (1ull << __popcll(live)) - 1ull;
   constexpr int D = TileShape<M>::D;
   const int lane = threadIdx.x & 63, r = lane >> 2, g = lane & 3;
   const int H = md.hidden;
   typename DEC::Stage* rows = S.stage;
   float mine = 0.0f;
+  if (ORDERED && blend) a = __shfl(a, order.from, 64);  // the weight of the point at this lane's place
 #pragma unroll
   for (int t = 0; t < 4; ++t) {
     if (((live >> (16 * t)) & 0xffffull) == 0) continue;
-    const int q = 16 * t + r;  // the group's point
+    const int q = ORDERED ? __shfl(order.from, 16 * t + r, 64) : 16 * t + r;  // the group's point
     float xq[3];
 #pragma unroll
     for (int k = 0; k < 3; ++k) xq[k] = __shfl(x[k], q, 64);
@@ -196,12 +226,13 @@ __device__ __forceinline__ float coop_eval(const ngl_model& md, const DecLds<DEC
 #pragma unroll
     for (int i = 0; i < D; ++i) acc[i] = 0.0f;
 #pragma unroll
-    for (int l = 1; l <= NGL_MAX_LODS; ++l)
-      if (l <= lod && md.nvox[l + 1] > 0) {
-        const int sh = Lp - l;
-        tile_level<M, FT>(md, l, __shfl(act ? vox[l - 1] : -1, q, 64), xq, qx >> sh, qy >> sh, qz >> sh, g, acc,
-                          l1s, l1);
-      }
+    for (int l = 1; l <= NGL_MAX_LODS; ++l) {
+      if (l > lod) break;
+      const int vq = __shfl(act ? vox[l - 1] : -1, q, 64);
+      if (__ballot(vq >= 0) == 0) break;
+      const int sh = Lp - l;
+      tile_level<M, FT>(md, l, vq, xq, qx >> sh, qy >> sh, qz >> sh, g, acc, l1s, l1);
+    }
     DEC::template tile_slice<D>(rows, r, g * D, acc);
     if (g == 0) DEC::tile_rest(rows, r, xq);
     wave_lds_sync();
@@ -210,16 +241,19 @@ __device__ __forceinline__ float coop_eval(const ngl_model& md, const DecLds<DEC
     if (blend) {
       // z_{L+1} = z_L + psi_{L+1}
       wave_lds_sync();
-      if (md.nvox[lod + 2] > 0) tile_level<M, FT>(md, lod + 1, __shfl(act ? vn : -1, q, 64), xq, qx, qy, qz, g, acc);
-      DEC::template tile_slice<D>(rows, r, g * D, acc);
-      wave_lds_sync();
+      const int vq = __shfl(act ? vn : -1, q, 64);
+      if (__ballot(vq >= 0) != 0) {
+        tile_level<M, FT>(md, lod + 1, vq, xq, qx, qy, qz, g, acc);
+        DEC::template tile_slice<D>(rows, r, g * D, acc);
+        wave_lds_sync();
+      }
       const float p1 = DEC::tile(S.frag1, S.w2s1, rows, H);
       out = (1.0f - a) * out + a * (b2b + p1);
     }
     wave_lds_sync();
-    if ((lane >> 4) == t) mine = out;  // lane 16 t + j owns point 16 t + j
+    if ((lane >> 4) == t) mine = out;  // lane 16 t + j has the point at place 16 t + j
   }
-  return mine;
+  return ORDERED ? __shfl(mine, order.rank, 64) : mine;
 }
 
 template <int M, typename FT, bool XYZ, int NW, class DEC>
@@ -230,9 +264,11 @@ __global__ __launch_bounds__(64 * NW) void k_query_coop(ngl_model md, const floa
   extern __shared__ __align__(16) char smem[];
   const int H = md.hidden;
   const bool blend = alpha_pp != nullptr || alpha > 0.0f;
-  DecLds<DEC> S(smem, H, blend, DEC::TILE_ELEMS);
+  constexpr bool STREAMED = !std::is_same<FT, F32>::value;
+  const int tile_bytes = STREAMED ? tile_lds_bytes<DEC>(blend ? lod + 1 : lod) : DEC::TILE_BYTES;
+  DecLds<DEC> S(smem, H, blend, tile_bytes / 4);
   // level 1's table after the staging rows (when the launch reserved it)
-  char* l1s = smem + DecLds<DEC>::fixed_bytes(H, blend) + NW * size_t(DEC::TILE_BYTES);
+  char* l1s = smem + DecLds<DEC>::fixed_bytes(H, blend) + NW * size_t(tile_bytes);
   DEC::load(md, lod, S.frag0, S.w2s0);
   if (blend) DEC::load(md, lod + 1, S.frag1, S.w2s1);
   if (l1) stage_l1<M, FT>(md, l1s);
@@ -258,8 +294,13 @@ __global__ __launch_bounds__(64 * NW) void k_query_coop(ngl_model md, const floa
       vlast = vn = -1;
     }
     const float a = act ? (alpha_pp ? alpha_pp[p] : alpha) : 0.0f;
-    const float out = coop_eval<M, FT, DEC>(md, S, x, vox, cx, cy, cz, vn, act, lod, Lp, blend, a, b2a, b2b, l1s,
-                                            l1);
+    float out;
+    if constexpr (STREAMED)
+      out = tile_eval<M, FT, DEC, true, true>(md, S, x, vox, pack_cell(cx, cy, cz), act, act && blend, a, lod, Lp, b2a,
+                                              b2b, l1s, l1, order_by_depth(vox, Lp, act));
+    else
+      out = coop_eval<M, FT, DEC, true>(md, S, x, vox, cx, cy, cz, vn, act, lod, Lp, blend, a, b2a, b2b, l1s, l1,
+                                        order_by_depth(vox, Lp, act));
     if (act) {
       sdf[p] = out;
       if (valid) valid[p] = vlast >= 0 ? 1 : 0;
@@ -300,7 +341,7 @@ static int launch_query_coop(const ngl_model& md, const float* x, int64_t P, int
                              float* sdf, uint8_t* valid, int32_t* vox, hipStream_t s) {
   const bool blend = app != nullptr || alpha > 0.0f;
   const size_t fixed = DecLds<DEC>::fixed_bytes(md.hidden, blend);
-  constexpr size_t R = DEC::TILE_BYTES;
+  const size_t R = std::is_same<FT, F32>::value ? DEC::TILE_BYTES : tile_lds_bytes<DEC>(blend ? lod + 1 : lod);
   if (fixed + 4 * R <= 65536)
     return launch_query_coop_nw<M, FT, XYZ, 4, DEC>(md, x, P, lod, alpha, app, sdf, valid, vox, s, fixed + 4 * R);
   if (fixed + 2 * R <= 65536)
@@ -550,7 +591,7 @@ __global__ __launch_bounds__(64 * NW) void k_normals_coop(ngl_model md, NormalAr
         for (int l = 0; l < NGL_MAX_LODS; ++l) vox[l] = -1;
         vn = -1;
       }
-      const float f = coop_eval<M, FT, DEC>(md, S, x, vox, cx, cy, cz, vn, act, lod, Lp, blend, A.alpha, b2a, b2b,
+      const float f = coop_eval<M, FT, DEC, false>(md, S, x, vox, cx, cy, cz, vn, act, lod, Lp, blend, A.alpha, b2a, b2b,
                                             l1s, A.l1);
       g[a] += sgn * f;
     }

@@ -108,12 +108,6 @@ __device__ __forceinline__ void ancestor_chain(const ngl_model& md, int v, int L
   }
 }
 
-// Packed cell at level l of the ancestor of the level-Lc cell c.
-__device__ __forceinline__ uint32_t cell_at(uint32_t c, int Lc, int l) {
-  const int sh = Lc - l;
-  return pack_cell(cell_x(c) >> sh, cell_y(c) >> sh, cell_z(c) >> sh);
-}
-
 // Ray served at queue position q: with an image width W (a multiple of 8,
 // the image a whole number of 8-row bands) the queue walks 8x8 pixel tiles
 // in row-major order, so 64 consecutive positions are a tile of
