@@ -29,16 +29,19 @@ static __global__ __launch_bounds__(kBlock) void k_radix_hist(const uint32_t* __
 }
 
 // Exclusive scan of n uint32 values in place by one block of 1024 lanes
-// (a must be 16-byte aligned); *total (nullable) receives the sum.  Each
+// (a must be 16-byte aligned); *total (nullable) receives the sum.  Block b
+// scans the array at a + b * stride (a multiple of 4), its sum in total[b].  Each
 // lane owns 32 consecutive values of a tile of 32 Ki values and loads them
 // as eight 16-byte vectors, so a tile's loads are all in flight together
 // (the radix-sort histograms, 256 x grid values, take a few tiles).
-static __global__ __launch_bounds__(1024) void k_scan_inplace(uint32_t* __restrict__ a, int64_t n, uint32_t* total) {
+static __global__ __launch_bounds__(1024) void k_scan_inplace(uint32_t* __restrict__ a, int64_t n, uint32_t* total,
+                                                            int64_t stride = 0) {
   constexpr int ITEMS = 32;
   __shared__ uint32_t part[16];
   __shared__ uint32_t carry_s;
   if (threadIdx.x == 0) carry_s = 0;
   __syncthreads();
+  a += blockIdx.x * stride;
   for (int64_t base = 0; base < n; base += 1024 * ITEMS) {
     uint32_t v[ITEMS];
     const int64_t b0 = base + int64_t(threadIdx.x) * ITEMS;
@@ -102,7 +105,7 @@ static __global__ __launch_bounds__(1024) void k_scan_inplace(uint32_t* __restri
     if (threadIdx.x == 0) carry_s += tot;
     __syncthreads();
   }
-  if (threadIdx.x == 0 && total) *total = carry_s;
+  if (threadIdx.x == 0 && total) total[blockIdx.x] = carry_s;
 }
 
 static __global__ __launch_bounds__(kBlock) void k_radix_scatter(const uint32_t* __restrict__ kin,
@@ -152,7 +155,7 @@ static __global__ __launch_bounds__(kBlock) void k_radix_scatter(const uint32_t*
 // Sorts n pairs on `bits` low key bits (ceil(bits / 8) passes) between the
 // two buffers; returns the index (0 or 1) of the buffer holding the result.
 // hist: 256 * grid words.
-inline int radix_sort_pairs(uint32_t* key[2], uint32_t* val[2], int64_t n, int bits, int grid, uint32_t* hist,
+inline int radix_sort_pairs(uint32_t* const key[2], uint32_t* const val[2], int64_t n, int bits, int grid, uint32_t* hist,
                             hipStream_t s) {
   int cur = 0;
   for (int shift = 0; shift < bits; shift += 8) {

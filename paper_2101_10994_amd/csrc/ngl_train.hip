@@ -2,22 +2,26 @@
 //
 // Feature gradients are accumulated without atomics, in a fixed order, so
 // results are bitwise reproducible:
-//   1. k_keys / radix sort: points are sorted by the Morton code of their
-//      finest cell.  Canonical voxel indices are Morton ranks, so this order
-//      groups the points of every voxel of every level contiguously.
+//   1. k_keys / radix sort (small batches: k_rank_sort): points are sorted by
+//      the Morton code of their finest cell.  Canonical voxel indices are
+//      Morton ranks, so this order groups the points of every voxel of every
+//      level contiguously.
 //   2. k_point: per point (in sorted order) the level sum z_L, each decoder's
 //      forward pass, the upstream gradient g_L, dz_L = W1_z^T (g_L w2 . 1[a>0])
 //      and the suffix sums dpsi_l = sum_{L>=l} dz_L (Eq. 2 reversed).
 //   3. k_dec_grad / k_dec_reduce: decoder gradients as per-block partial sums
 //      over fixed point ranges, reduced in block order.
-//   4. per level: k_rec_count / scan / k_rec_write reduce fixed tiles of 64
-//      sorted points into per-(voxel, tile) records of sum_p w_j(p) dpsi_l(p);
-//      k_vox_reduce sums each voxel's records; k_corner gathers, for every
-//      corner, the partials of the (voxel, slot) pairs that share it.
+//   4. all levels in one launch each: k_rec_count / scan / k_rec_write reduce
+//      fixed tiles of 64 sorted points into per-(voxel, tile) records of
+//      sum_p w_j(p) dpsi_l(p); k_vox_reduce sums each voxel's records; k_corner
+//      gathers, for every corner, the partials of the (voxel, slot) pairs that
+//      share it.  Small batches touch few voxels: k_corner<M, true> reads the
+//      records themselves.
 #include "ngl_common.h"
 
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 #include "ngl_device.h"
 #include "ngl_sort.h"
 
@@ -37,6 +41,13 @@ constexpr int kTile = 64;       // sorted points per record tile (one wavefront)
 // per point (k_point_wave): a lane per point would leave most of the chip
 // idle and each lane's serial decoder work would set the step time.
 constexpr int64_t kPointWaveMax = 16384;
+// Batches up to this many points are sorted by ranks in one launch
+// (k_rank_sort, P^2 comparisons on all keys in LDS, against ten radix
+// launches of one to four blocks), and each record tile counts the records
+// before it itself: launches are what a small step spends its time on.  A
+// step of 512 points with Adam took 323 us and takes 87, with the scan, the
+// record and the loss launches of each level folded into one.
+constexpr int64_t kRankSortMax = 4096;
 
 __device__ inline uint32_t spread3_10(uint32_t v) {
   v &= 0x3ffu;
@@ -50,18 +61,51 @@ __device__ inline uint32_t spread3_10(uint32_t v) {
 // ---------------------------------------------------------------------------
 // 1. sort keys and a stable LSD radix sort (8-bit digits)
 // ---------------------------------------------------------------------------
+__device__ inline uint32_t point_key(const float* xs, int64_t P, int64_t p, int D) {
+  const float x = xs[p], y = xs[P + p], z = xs[2 * P + p];
+  if (!in_box(x, y, z)) return 1u << (3 * D);  // after every cell
+  const int r = 1 << D;
+  return spread3_10(cell_of(x, r)) | spread3_10(cell_of(y, r)) << 1 | spread3_10(cell_of(z, r)) << 2;
+}
+
 __global__ __launch_bounds__(kBlock) void k_keys(const float* __restrict__ xs, int64_t P, int D,
                                                  uint32_t* __restrict__ key, uint32_t* __restrict__ val) {
   const int64_t p = int64_t(blockIdx.x) * kBlock + threadIdx.x;
   if (p >= P) return;
-  const float x = xs[p], y = xs[P + p], z = xs[2 * P + p];
-  uint32_t k = 1u << (3 * D);  // outside the box: after every cell
-  if (in_box(x, y, z)) {
-    const int r = 1 << D;
-    k = spread3_10(cell_of(x, r)) | spread3_10(cell_of(y, r)) << 1 | spread3_10(cell_of(z, r)) << 2;
-  }
-  key[p] = k;
+  key[p] = point_key(xs, P, p, D);
   val[p] = uint32_t(p);
+}
+
+// The stable order of up to kRankSortMax keys: sidx[rank] = point, the rank
+// of a point being the number of points with a smaller key, or the same key
+// and a smaller index.  Each block holds every key in LDS and ranks 64
+// points, its four wavefronts a quarter of the comparisons each.  On the way
+// clear[0, nclear) = 0 (the voxels' first records).
+__global__ __launch_bounds__(kBlock) void k_rank_sort(const float* __restrict__ xs, int P, int D,
+                                                      uint32_t* __restrict__ sidx, uint32_t* __restrict__ clear,
+                                                      int64_t nclear) {
+  __shared__ uint32_t key[kRankSortMax];
+  __shared__ int part[kBlock / 64][64];
+  for (int64_t i = int64_t(blockIdx.x) * kBlock + threadIdx.x; i < nclear; i += int64_t(gridDim.x) * kBlock) clear[i] = 0;
+  for (int p = threadIdx.x; p < P; p += kBlock) key[p] = point_key(xs, P, p, D);
+  __syncthreads();
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int me = int(blockIdx.x) * 64 + lane;
+  const uint32_t mine = me < P ? key[me] : 0u;
+  const int quarter = (P + kBlock / 64 - 1) / (kBlock / 64);
+  const int begin = w * quarter, end = min(begin + quarter, P);
+  int rank = 0;
+#pragma unroll 8
+  for (int q = begin; q < end; ++q) {
+    const uint32_t k = key[q];
+    rank += (k < mine || (k == mine && q < me)) ? 1 : 0;
+  }
+  part[w][lane] = rank;
+  __syncthreads();
+  if (w == 0 && me < P) {
+    for (int q = 1; q < kBlock / 64; ++q) rank += part[q][lane];
+    sidx[rank] = uint32_t(me);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -227,35 +271,48 @@ __global__ __launch_bounds__(kBlock) void k_point(ngl_model md, PointArgs A) {
 }
 
 // Small batches (fewer points than lanes to keep busy): one wavefront per
-// sorted point, the same quantities as k_point.  Lanes split each level's
-// gather (lane = corner j * 8 + slice: 8 corners x M/8 features), the
-// decoders' hidden units (unit k = lane + 64 u) and the adjoint
-// (lane = output i + M * part, parts summing strided unit ranges); the
-// partial sums are combined by fixed butterflies, so results are
-// deterministic.  The squared residual of each point goes to loss_part[p].
+// sorted point and LOD (the levels' features up to it are gathered together,
+// then decoder LOD runs), the same quantities as k_point except that drows
+// receives dz_L (k_rec_write adds the LODs).  Lanes split each level's gather
+// (lane = corner j * 8 + slice: 8 corners x M/8 features), the hidden units
+// (unit k = lane + 64 u) and the adjoint (lane = output i + M * part, parts
+// summing strided unit ranges); the partial sums are combined by fixed
+// butterflies, so results are deterministic.  The weighted squared residual
+// goes to loss_part[LOD][p].  STAGED: the block's four wavefronts share the
+// decoder's first layer in LDS, read by lane without bank conflicts (an odd
+// row length), where rows read from memory take a cache line per lane.
+// Bound by the latency of one point's chain.
 __device__ inline void wave_sync_lds() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-template <int M, bool XYZ, bool TRAIN>
+template <int M, bool XYZ, bool TRAIN, bool STAGED>
 __global__ __launch_bounds__(kBlock) void k_point_wave(ngl_model md, PointArgs A) {
   constexpr int OFF = XYZ ? 3 : 0;
   constexpr int DIN = M + OFF;
+  constexpr int WR = DIN | 1;      // staged row: odd
   constexpr int FE = M / 8;        // gather: features per lane (8 lanes per corner row)
   constexpr int KP = 64 / M;       // adjoint: lanes per output
   constexpr int UMAX = NGL_MAX_HIDDEN / 64;
+  extern __shared__ float w_s[];   // STAGED: [H][WR]
   __shared__ float zsh[kBlock / 64][M];
   __shared__ float gash[kBlock / 64][NGL_MAX_HIDDEN];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int64_t p = int64_t(blockIdx.x) * (kBlock / 64) + w;
   const int64_t P = A.P;
+  const int Lm = md.num_lods;
+  const int H = md.hidden;
+  const int L = blockIdx.y + 1;
+  const float* W1 = static_cast<const float*>(md.W1[L - 1]);
+  if constexpr (STAGED) {
+    for (int e = threadIdx.x; e < H * DIN; e += kBlock) w_s[e / DIN * WR + e % DIN] = W1[e];
+    __syncthreads();
+  }
   if (p >= P) return;  // wave-uniform: no block-wide barrier below
   const int64_t id = A.sidx[p];
   const float x[3] = {A.xs[id], A.xs[P + id], A.xs[2 * P + id]};
-  const int Lm = md.num_lods;
-  const int H = md.hidden;
   int vox[NGL_MAX_LODS];
   int cx = 0, cy = 0, cz = 0;
   if (in_box(x[0], x[1], x[2])) {
@@ -271,122 +328,121 @@ __global__ __launch_bounds__(kBlock) void k_point_wave(ngl_model md, PointArgs A
   const float tgt = TRAIN ? A.target[id] : 0.0f;
   const int j = lane >> 3, sl = lane & 7;        // gather: corner, slice
   const int oi = lane % M, part = lane / M;      // adjoint: output, part
+  // psi_1..psi_L: corner j's slices, requested for every level together (a
+  // level without a voxel reads voxel 0's row and is left out of the sum)
+  float row[NGL_MAX_LODS][FE];
+  int corner[NGL_MAX_LODS];
+#pragma unroll
+  for (int l = 1; l <= NGL_MAX_LODS; ++l) {
+    corner[l - 1] = 0;
+    if (l <= L && md.nvox[l + 1] > 0)
+      corner[l - 1] = md.corners[l - 1][int64_t(vox[l - 1] >= 0 ? vox[l - 1] : 0) * 8 + j];
+  }
+#pragma unroll
+  for (int l = 1; l <= NGL_MAX_LODS; ++l) {
+    if (l <= L && md.nvox[l + 1] > 0) {
+      const float* r = static_cast<const float*>(md.feat[l - 1]) + int64_t(corner[l - 1]) * M + sl * FE;
+#pragma unroll
+      for (int e = 0; e < FE; ++e) row[l - 1][e] = r[e];
+    }
+  }
   float zl[FE];                                  // this lane's slice of z_L
 #pragma unroll
   for (int e = 0; e < FE; ++e) zl[e] = 0.0f;
-  float dzl[NGL_MAX_LODS];                       // dz_L[oi] (part 0 lanes)
-  float lossacc = 0.0f;
 #pragma unroll
   for (int l = 1; l <= NGL_MAX_LODS; ++l) {
-    dzl[l - 1] = 0.0f;
-    if (l > Lm) continue;
+    if (l > L || vox[l - 1] < 0) continue;
     const int s = Lm - l;
-    // psi_l: corner j's slice weighted, summed over the 8 corners
-    if (vox[l - 1] >= 0) {
-      float u[3];
-      cell_local(l, cx >> s, cy >> s, cz >> s, x, u);
-      const int c = md.corners[l - 1][int64_t(vox[l - 1]) * 8 + j];
-      const float wj = corner_weight(u, j);
-      const float* row = static_cast<const float*>(md.feat[l - 1]) + int64_t(c) * M + sl * FE;
-      float t[FE];
+    float u[3];
+    cell_local(l, cx >> s, cy >> s, cz >> s, x, u);
+    const float wj = corner_weight(u, j);
+    float t[FE];
 #pragma unroll
-      for (int e = 0; e < FE; ++e) t[e] = wj * row[e];
+    for (int e = 0; e < FE; ++e) t[e] = wj * row[l - 1][e];
 #pragma unroll
-      for (int off = 8; off < 64; off <<= 1)
+    for (int off = 8; off < 64; off <<= 1)
 #pragma unroll
-        for (int e = 0; e < FE; ++e) t[e] += __shfl_xor(t[e], off, 64);
+      for (int e = 0; e < FE; ++e) t[e] += __shfl_xor(t[e], off, 64);
 #pragma unroll
-      for (int e = 0; e < FE; ++e) zl[e] += t[e];
-    }
-    if (lane == 0) A.vox_s[int64_t(l - 1) * P + p] = vox[l - 1];
-    if (lane < 8) {
+    for (int e = 0; e < FE; ++e) zl[e] += t[e];
+  }
+  if (lane == 0) A.vox_s[int64_t(L - 1) * P + p] = pick<NGL_MAX_LODS>(vox, L - 1);
+  if (lane < 8) {
 #pragma unroll
-      for (int e = 0; e < FE; ++e) zsh[w][sl * FE + e] = zl[e];
-    }
-    wave_sync_lds();
-    float z[M];
+    for (int e = 0; e < FE; ++e) zsh[w][sl * FE + e] = zl[e];
+  }
+  wave_sync_lds();
+  float z[M];
 #pragma unroll
-    for (int q = 0; q < M; ++q) z[q] = zsh[w][q];
-    if (lane < M) A.zrows[(int64_t(l - 1) * P + p) * M + lane] = zsh[w][lane];
-    // decoder L = l, units k = lane + 64 u
-    const float* W1 = static_cast<const float*>(md.W1[l - 1]);
-    const float* b1 = md.b1[l - 1];
-    const float* w2 = md.w2[l - 1];
-    float part_out = 0.0f;
-    float ga[UMAX];
+  for (int q = 0; q < M; ++q) z[q] = zsh[w][q];
+  if (lane < M) A.zrows[(int64_t(L - 1) * P + p) * M + lane] = zsh[w][lane];
+  // decoder L, units k = lane + 64 u
+  const float* b1 = md.b1[L - 1];
+  const float* w2 = md.w2[L - 1];
+  float part_out = 0.0f;
+  float ga[UMAX];
 #pragma unroll
-    for (int uu = 0; uu < UMAX; ++uu) {
-      ga[uu] = 0.0f;
-      const int k = lane + 64 * uu;
-      if (k < H) {
-        const float* rw = W1 + k * DIN;
-        float a = b1[k];
-        if constexpr (XYZ) {
-          a = fmaf(rw[0], x[0], a);
-          a = fmaf(rw[1], x[1], a);
-          a = fmaf(rw[2], x[2], a);
-        }
-#pragma unroll
-        for (int i = 0; i < M; ++i) a = fmaf(rw[OFF + i], z[i], a);
-        part_out = fmaf(w2[k], fmaxf(a, 0.0f), part_out);
-        ga[uu] = a > 0.0f ? w2[k] : 0.0f;  // times g below
+  for (int uu = 0; uu < UMAX; ++uu) {
+    ga[uu] = 0.0f;
+    const int k = lane + 64 * uu;
+    if (k < H) {
+      const float* rw = STAGED ? w_s + k * WR : W1 + k * DIN;
+      float a = b1[k];
+      if constexpr (XYZ) {
+        a = fmaf(rw[0], x[0], a);
+        a = fmaf(rw[1], x[1], a);
+        a = fmaf(rw[2], x[2], a);
       }
-    }
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) part_out += __shfl_xor(part_out, off, 64);
-    const float out = md.b2[l - 1] + part_out;
-    float g;
-    if constexpr (TRAIN) {
-      const float wres = A.lod_w[l - 1] * (out - tgt);
-      lossacc = fmaf(wres, out - tgt, lossacc);
-      g = 2.0f * wres * A.inv_p;
-    } else {
-      g = A.grad[int64_t(l - 1) * P + id];
-    }
-    if (lane == 0) {
-      if (A.sdf_all) A.sdf_all[int64_t(l - 1) * P + id] = out;
-      A.gs[int64_t(l - 1) * P + p] = g;
-    }
-    // dz = W1_z^T (g w2 . 1[a > 0]): ga to LDS, lane (oi, part) sums units
-    // part, part + KP, ...
-#pragma unroll
-    for (int uu = 0; uu < UMAX; ++uu) {
-      const int k = lane + 64 * uu;
-      if (k < H) gash[w][k] = g * ga[uu];
-    }
-    wave_sync_lds();
-    float d = 0.0f;
-    for (int k = part; k < H; k += KP) d = fmaf(W1[k * DIN + OFF + oi], gash[w][k], d);
-#pragma unroll
-    for (int off = M; off < 64; off <<= 1) d += __shfl_xor(d, off, 64);
-    dzl[l - 1] = d;
-    wave_sync_lds();  // zsh and gash are rewritten by the next level
-  }
-  // dpsi_l = sum_{L >= l} dz_L, from the finest level down
-  if (lane < M) {
-    float acc = 0.0f;
-#pragma unroll
-    for (int l = NGL_MAX_LODS; l >= 1; --l) {
-      if (l > Lm) continue;
-      acc = l == Lm ? dzl[l - 1] : acc + dzl[l - 1];
-      A.drows[(int64_t(l - 1) * P + p) * M + lane] = acc;
+      for (int i = 0; i < M; ++i) a = fmaf(rw[OFF + i], z[i], a);
+      part_out = fmaf(w2[k], fmaxf(a, 0.0f), part_out);
+      ga[uu] = a > 0.0f ? w2[k] : 0.0f;  // times g below
     }
   }
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) part_out += __shfl_xor(part_out, off, 64);
+  const float out = md.b2[L - 1] + part_out;
+  float g, wres = 0.0f;
   if constexpr (TRAIN) {
-    if (lane == 0) A.loss_part[p] = lossacc;
+    wres = A.lod_w[L - 1] * (out - tgt);
+    g = 2.0f * wres * A.inv_p;
+  } else {
+    g = A.grad[int64_t(L - 1) * P + id];
   }
+  if (lane == 0) {
+    if (A.sdf_all) A.sdf_all[int64_t(L - 1) * P + id] = out;
+    A.gs[int64_t(L - 1) * P + p] = g;
+    if constexpr (TRAIN) A.loss_part[int64_t(L - 1) * P + p] = wres * (out - tgt);
+  }
+  // dz = W1_z^T (g w2 . 1[a > 0]): ga to LDS, lane (oi, part) sums units
+  // part, part + KP, ...
+#pragma unroll
+  for (int uu = 0; uu < UMAX; ++uu) {
+    const int k = lane + 64 * uu;
+    if (k < H) gash[w][k] = g * ga[uu];
+  }
+  wave_sync_lds();
+  float d = 0.0f;
+#pragma unroll 4
+  for (int k = part; k < H; k += KP) d = fmaf(STAGED ? w_s[k * WR + OFF + oi] : W1[k * DIN + OFF + oi], gash[w][k], d);
+#pragma unroll
+  for (int off = M; off < 64; off <<= 1) d += __shfl_xor(d, off, 64);
+  if (lane < M) A.drows[(int64_t(L - 1) * P + p) * M + lane] = d;
 }
 
-__global__ __launch_bounds__(kBlock) void k_loss_reduce(const float* __restrict__ part, int n, float inv_p,
-                                                        float* __restrict__ loss) {
-  __shared__ float sp[kBlock];
+// *loss = inv_p * sum of part[0, n) in a fixed order, by the whole block.
+__device__ inline void loss_reduce(const float* part, int64_t n, float inv_p, float* loss) {
+  __shared__ float sp[kBlock / 64];
   float s = 0.0f;
-  for (int i = threadIdx.x; i < n; i += kBlock) s += part[i];
-  sp[threadIdx.x] = s;
+  for (int64_t i = threadIdx.x; i < n; i += kBlock) s += part[i];
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
+  if ((threadIdx.x & 63) == 0) sp[threadIdx.x >> 6] = s;
   __syncthreads();
   if (threadIdx.x == 0) {
     float t = 0.0f;
-    for (int i = 0; i < kBlock; ++i) t += sp[i];
+#pragma unroll
+    for (int i = 0; i < kBlock / 64; ++i) t += sp[i];
     *loss = t * inv_p;
   }
 }
@@ -484,6 +540,10 @@ struct DecOut {
   float* db1[NGL_MAX_LODS];
   float* dw2[NGL_MAX_LODS];
   float* db2;
+  float* loss;             // nullable: the sum of loss_part[0, nloss) times inv_p
+  const float* loss_part;
+  int64_t nloss;
+  float inv_p;
 };
 
 // Each wavefront sums one output entry's nblk * PH partials: lane i takes
@@ -494,6 +554,10 @@ __global__ __launch_bounds__(kBlock) void k_dec_reduce(const float* __restrict__
                                                        const float* __restrict__ part_b2, int H, int din, int PH,
                                                        int nblk, DecOut O) {
   const int L = blockIdx.y + 1;
+  if (blockIdx.x == gridDim.x - 1) {  // the block after the entries
+    if (L == 1 && O.loss) loss_reduce(O.loss_part, O.nloss, O.inv_p, O.loss);
+    return;
+  }
   const int lane = threadIdx.x & 63;
   const int e = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);  // entry of [H][din+2]
   const int W = din + 2;
@@ -522,50 +586,101 @@ __global__ __launch_bounds__(kBlock) void k_dec_reduce(const float* __restrict__
 }
 
 // ---------------------------------------------------------------------------
-// 4. feature gradients of one level: tile records, voxel sums, corner gather
+// 4. feature gradients: tile records, voxel sums, corner gather.  All levels in
+// one launch: a level alone leaves most of the chip idle at the coarse ones
+// (2^19 points, 5 levels: records 253 -> 124 us, voxel sums 90 -> 57, scans
+// 113 -> 58).
 // ---------------------------------------------------------------------------
-struct LevelArgs {
+struct FeatArgs {
   const float* xs;
   int64_t P;
-  int lvl;
+  int Lm;
+  int64_t ntiles;
   const uint32_t* sidx;
-  const int32_t* vox_s;   // [P] this level, sorted order
-  const float* drows;     // [P][M] this level, sorted order
-  uint32_t* rec_cnt;      // [ntiles] counts, then exclusive offsets
-  uint32_t* rec_total;    // [1]
-  int32_t* rec_key;       // [maxrec] voxel of each record (ascending)
-  float* recs;            // [maxrec][8][M]
-  int64_t maxrec;
-  float* vpart;           // [nv][8][M]
+  const int32_t* vox_s;   // [L][P] sorted order
+  const float* drows;     // [L][P][M] sorted order: dpsi_l, or dz_L (k_rec_write)
+  uint32_t* rec_cnt;      // [L][cnt_stride] counts, then exclusive offsets
+  int64_t cnt_stride;
+  uint32_t* rec_total;    // [L]
+  int32_t* rec_key;       // level l at rec_off[l]: voxel of each record (ascending)
+  float* recs;            // level l at rec_off[l] * 8 M: [maxrec][8][M]
+  int64_t rec_off[NGL_MAX_LODS + 1];
+  float* vpart;           // level l at vox_off[l] * 8 M: [nv][8][M]
+  uint32_t* vfirst;       // level l at vox_off[l]: index + 1 of the voxel's first record, 0 without
+  int64_t vox_off[NGL_MAX_LODS + 1];
+  int64_t corner_off[NGL_MAX_LODS + 1];
+  const int32_t* adj_off[NGL_MAX_LODS];
+  const int32_t* adj[NGL_MAX_LODS];
+  float* dfeat[NGL_MAX_LODS];
 };
 
-// Records of a tile: one per run of equal (existing) voxels.
-__global__ __launch_bounds__(64) void k_rec_count(LevelArgs A) {
-  const int64_t p = int64_t(blockIdx.x) * kTile + threadIdx.x;
-  const int32_t v = p < A.P ? A.vox_s[p] : -1;
-  const int32_t prev = (threadIdx.x > 0 && p < A.P) ? A.vox_s[p - 1] : -1;
-  const bool head = v >= 0 && v != prev;
-  const uint64_t heads = __ballot(head);
-  if (threadIdx.x == 0) A.rec_cnt[blockIdx.x] = uint32_t(__popcll(heads));
+// The level whose range of `off` holds i.
+__device__ inline int level_of(const int64_t* off, int Lm, int64_t i) {
+  int l = 0;
+  while (l + 1 < Lm && i >= off[l + 1]) ++l;
+  return l;
 }
 
-// STAGE (small batches, few tiles in flight): the tile's dpsi rows are
-// loaded into LDS together before the sequential pass.
-template <int M, bool STAGE>
-__global__ __launch_bounds__(64) void k_rec_write(ngl_model md, LevelArgs A) {
-  __shared__ float w_s[kTile][8];
-  __shared__ int32_t v_s[kTile];
-  __shared__ uint32_t r_s[kTile];
-  __shared__ float d_s[STAGE ? kTile * M : 1];
+// Records of a tile: one per run of equal (existing) voxels.
+__global__ __launch_bounds__(64) void k_rec_count(FeatArgs A) {
+  const int32_t* vox = A.vox_s + int64_t(blockIdx.y) * A.P;
+  const int64_t p = int64_t(blockIdx.x) * kTile + threadIdx.x;
+  const int32_t v = p < A.P ? vox[p] : -1;
+  const int32_t prev = __shfl_up(v, 1, 64);
+  const uint64_t heads = __ballot(v >= 0 && (threadIdx.x == 0 || v != prev));
+  if (threadIdx.x == 0) A.rec_cnt[blockIdx.y * A.cnt_stride + blockIdx.x] = uint32_t(__popcll(heads));
+}
+
+// One wavefront per tile and level.  DZ: the rows of drows are the dz_L,
+// summed here from the finest LOD down (dpsi_l = sum_{L >= l} dz_L).  FEW (up
+// to kRankSortMax points): the tile counts the records of the tiles before it
+// itself, and the voxels' first records are noted.  Bound by the latency of
+// the tile's chain, so the levels run side by side.
+template <int M, bool DZ, bool FEW>
+__global__ __launch_bounds__(64) void k_rec_write(ngl_model md, FeatArgs A) {
+  __shared__ __align__(16) float w_s[kTile][8];
+  __shared__ __align__(16) float d_s[kTile * M];
   const int lane = threadIdx.x;
-  const int64_t p = int64_t(blockIdx.x) * kTile + lane;
-  const int lvl = A.lvl;
+  const int l = blockIdx.y, lvl = l + 1;
+  const int32_t* vox = A.vox_s + int64_t(l) * A.P;
+  const int64_t p0 = int64_t(blockIdx.x) * kTile, p = p0 + lane;
+  const int n = int(A.P - p0 < kTile ? A.P - p0 : kTile);
+  // the tile's dpsi rows, requested together
+  constexpr int NQ = M / 4;  // 16-byte vectors per lane
+  float4 rows[NQ];
+  {
+    const float4* src = reinterpret_cast<const float4*>(A.drows + (int64_t(DZ ? A.Lm - 1 : l) * A.P + p0) * M);
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+      const int e = lane + 64 * q;
+      rows[q] = e < n * NQ ? src[e] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    }
+  }
   // phase A, lane = point: voxel, trilinear weights and record slot
-  const int32_t v = p < A.P ? A.vox_s[p] : -1;
-  const int32_t prev = (lane > 0 && p < A.P) ? A.vox_s[p - 1] : -1;
-  const bool head = v >= 0 && v != prev;
-  const uint64_t heads = __ballot(head);
-  const uint32_t rec = A.rec_cnt[blockIdx.x] + uint32_t(__popcll(heads & ((2ull << lane) - 1ull))) - 1u;
+  uint32_t base;
+  if constexpr (FEW) {
+    int before = 0;
+    for (int t = 0; t < int(blockIdx.x); t += 8) {
+      int32_t u[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) u[q] = t + q < int(blockIdx.x) ? vox[(t + q) * kTile + lane] : -1;
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const int32_t up = __shfl_up(u[q], 1, 64);
+        before += __popcll(__ballot(u[q] >= 0 && (lane == 0 || u[q] != up)));
+      }
+    }
+    base = uint32_t(before);
+  } else {
+    base = A.rec_cnt[l * A.cnt_stride + blockIdx.x];
+  }
+  const int32_t v = p < A.P ? vox[p] : -1;
+  const int32_t prev = __shfl_up(v, 1, 64);
+  const uint64_t valid = __ballot(v >= 0);
+  const uint64_t heads = __ballot(v >= 0 && (lane == 0 || v != prev));
+  // last points of the runs: the next point starts another run or has no voxel
+  const uint64_t ends = valid & (heads >> 1 | ~(valid >> 1) | 1ull << 63);
+  if (FEW && int64_t(blockIdx.x) == A.ntiles - 1 && lane == 0) A.rec_total[l] = base + uint32_t(__popcll(heads));
   float wj[8];
 #pragma unroll
   for (int j = 0; j < 8; ++j) wj[j] = 0.0f;
@@ -573,68 +688,91 @@ __global__ __launch_bounds__(64) void k_rec_write(ngl_model md, LevelArgs A) {
     const int64_t id = A.sidx[p];
     const float x[3] = {A.xs[id], A.xs[A.P + id], A.xs[2 * A.P + id]};
     const uint32_t c = md.cell[lvl + 1][v];
-    const int ci[3] = {cell_x(c), cell_y(c), cell_z(c)};
-    const int r = 4 << (lvl - 1);
-    const float step = 2.0f / float(r);
-    const float half_r = 0.5f * float(r);
     float u[3];
+    cell_local(lvl, cell_x(c), cell_y(c), cell_z(c), x, u);
 #pragma unroll
-    for (int a = 0; a < 3; ++a) u[a] = fminf(fmaxf((x[a] - (-1.0f + float(ci[a]) * step)) * half_r, 0.0f), 1.0f);
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-      wj[j] = ((j & 1) ? u[0] : 1.0f - u[0]) * ((j & 2) ? u[1] : 1.0f - u[1]) * ((j & 4) ? u[2] : 1.0f - u[2]);
+    for (int j = 0; j < 8; ++j) wj[j] = corner_weight(u, j);
   }
+  int32_t* keys = A.rec_key + A.rec_off[l];
+  const int64_t maxrec = A.rec_off[l + 1] - A.rec_off[l];
+  if (heads >> lane & 1ull) {
+    const int64_t r = int64_t(base) + __popcll(heads & ((1ull << lane) - 1ull));
+    if (r < maxrec) keys[r] = v;
+    // the voxel's first record, unless the tile before ends in the voxel
+    if (FEW && (lane > 0 || p0 == 0 || vox[p0 - 1] != v)) A.vfirst[A.vox_off[l] + v] = uint32_t(r) + 1u;
+  }
+  if constexpr (DZ) {
+    for (int k = A.Lm - 2; k >= l; --k) {
+      const float4* src = reinterpret_cast<const float4*>(A.drows + (int64_t(k) * A.P + p0) * M);
+      float4 t[NQ];
 #pragma unroll
-  for (int j = 0; j < 8; ++j) w_s[lane][j] = wj[j];
-  v_s[lane] = v;
-  r_s[lane] = rec;
-  const int n = int(A.P - int64_t(blockIdx.x) * kTile < kTile ? A.P - int64_t(blockIdx.x) * kTile : kTile);
-  if constexpr (STAGE) {
-    const float* src = A.drows + int64_t(blockIdx.x) * kTile * M;
+      for (int q = 0; q < NQ; ++q) {
+        const int e = lane + 64 * q;
+        t[q] = e < n * NQ ? src[e] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+      }
 #pragma unroll
-    for (int q = 0; q < M; ++q) {
-      const int e = lane + 64 * q;
-      if (e < n * M) d_s[e] = src[e];
+      for (int q = 0; q < NQ; ++q) rows[q].x += t[q].x, rows[q].y += t[q].y, rows[q].z += t[q].z, rows[q].w += t[q].w;
     }
   }
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) reinterpret_cast<float4*>(d_s)[lane + 64 * q] = rows[q];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) w_s[lane][j] = wj[j];
   __syncthreads();
   // phase B, lane = (channel, slot group): sequential over the tile's points
   constexpr int SG = 64 / M;      // slot groups
   constexpr int SPL = 8 / SG;     // slots per lane
   const int ch = lane % M;
   const int sg = lane / M;
+  float* recs = A.recs + A.rec_off[l] * 8 * M;
   float acc[SPL];
 #pragma unroll
   for (int s = 0; s < SPL; ++s) acc[s] = 0.0f;
+  int64_t r = base;
+  float row = d_s[ch], w[SPL];  // of the next point
+#pragma unroll
+  for (int s = 0; s < SPL; ++s) w[s] = w_s[0][sg * SPL + s];
   for (int i = 0; i < n; ++i) {
-    const int32_t vi = v_s[i];
-    if (vi < 0) continue;
-    const float row = STAGE ? d_s[i * M + ch] : A.drows[(int64_t(blockIdx.x) * kTile + i) * M + ch];
+    const float row_i = row;
+    float w_i[SPL];
 #pragma unroll
-    for (int s = 0; s < SPL; ++s) acc[s] = fmaf(w_s[i][sg * SPL + s], row, acc[s]);
-    if (i == n - 1 || v_s[i + 1] != vi) {
-      const uint32_t r = r_s[i];
-      if (int64_t(r) < A.maxrec) {
+    for (int s = 0; s < SPL; ++s) w_i[s] = w[s];
+    const int next = i + 1 < kTile ? i + 1 : i;
+    row = d_s[next * M + ch];
 #pragma unroll
-        for (int s = 0; s < SPL; ++s) A.recs[(int64_t(r) * 8 + sg * SPL + s) * M + ch] = acc[s];
-        if (lane == 0) A.rec_key[r] = vi;
+    for (int s = 0; s < SPL; ++s) w[s] = w_s[next][sg * SPL + s];
+    if (!(valid >> i & 1ull)) continue;
+#pragma unroll
+    for (int s = 0; s < SPL; ++s) acc[s] = fmaf(w_i[s], row_i, acc[s]);
+    if (ends >> i & 1ull) {
+      if (r < maxrec) {
+#pragma unroll
+        for (int s = 0; s < SPL; ++s) recs[(r * 8 + sg * SPL + s) * M + ch] = acc[s];
       }
+      ++r;
 #pragma unroll
       for (int s = 0; s < SPL; ++s) acc[s] = 0.0f;
     }
   }
 }
 
-// Sum of each voxel's records (ascending record order), one wavefront per voxel.
+// Sum of each voxel's records (ascending record order), one wavefront per
+// voxel of every level.
 template <int M>
-__global__ __launch_bounds__(64) void k_vox_reduce(LevelArgs A, int64_t nv) {
-  const int64_t v = blockIdx.x;
-  if (v >= nv) return;
-  const int64_t nrec = *A.rec_total < A.maxrec ? *A.rec_total : A.maxrec;
+__global__ __launch_bounds__(kBlock) void k_vox_reduce(FeatArgs A) {
+  const int64_t g = int64_t(blockIdx.x) * (kBlock / 64) + (threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  if (g >= A.vox_off[A.Lm]) return;
+  const int l = level_of(A.vox_off, A.Lm, g);
+  const int64_t v = g - A.vox_off[l];
+  const int32_t* keys = A.rec_key + A.rec_off[l];
+  const float* recs = A.recs + A.rec_off[l] * 8 * M;
+  const int64_t maxrec = A.rec_off[l + 1] - A.rec_off[l];
+  const int64_t nrec = A.rec_total[l] < maxrec ? A.rec_total[l] : maxrec;
   int64_t lo = 0, hi = nrec;
   while (lo < hi) {
     const int64_t mid = (lo + hi) >> 1;
-    if (A.rec_key[mid] < v) lo = mid + 1;
+    if (keys[mid] < v) lo = mid + 1;
     else hi = mid;
   }
   constexpr int PER = 8 * M / 64;
@@ -648,7 +786,7 @@ __global__ __launch_bounds__(64) void k_vox_reduce(LevelArgs A, int64_t nv) {
     int64_t a = lo;
     while (a < hi) {
       const int64_t mid = (a + hi) >> 1;
-      if (A.rec_key[mid] <= v) a = mid + 1;
+      if (keys[mid] <= v) a = mid + 1;
       else hi = mid;
     }
   }
@@ -658,7 +796,7 @@ __global__ __launch_bounds__(64) void k_vox_reduce(LevelArgs A, int64_t nv) {
 #pragma unroll
     for (int k = 0; k < 8; ++k)
 #pragma unroll
-      for (int s = 0; s < PER; ++s) t[k][s] = A.recs[(r + k) * 8 * M + s * 64 + threadIdx.x];
+      for (int s = 0; s < PER; ++s) t[k][s] = recs[(r + k) * 8 * M + s * 64 + lane];
 #pragma unroll
     for (int k = 0; k < 8; ++k)
 #pragma unroll
@@ -666,25 +804,53 @@ __global__ __launch_bounds__(64) void k_vox_reduce(LevelArgs A, int64_t nv) {
   }
   for (; r < hi; ++r) {
 #pragma unroll
-    for (int s = 0; s < PER; ++s) acc[s] += A.recs[r * 8 * M + s * 64 + threadIdx.x];
+    for (int s = 0; s < PER; ++s) acc[s] += recs[r * 8 * M + s * 64 + lane];
   }
 #pragma unroll
-  for (int s = 0; s < PER; ++s) A.vpart[v * 8 * M + s * 64 + threadIdx.x] = acc[s];
+  for (int s = 0; s < PER; ++s) A.vpart[g * 8 * M + s * 64 + lane] = acc[s];
 }
 
-// dZ_l[c][ch] = sum over (v, j) sharing corner c of vpart[v][j][ch].
-template <int M>
-__global__ __launch_bounds__(kBlock) void k_corner(const int32_t* __restrict__ adj_off,
-                                                   const int32_t* __restrict__ adj,
-                                                   const float* __restrict__ vpart, int64_t nc,
-                                                   float* __restrict__ dfeat) {
+// dZ_l[c][ch] = sum over (v, j) sharing corner c of the voxel sums of
+// (v, j, ch), four channels per thread.  FEW: a voxel's sum is taken from
+// its records here (few voxels have any), else from vpart.
+template <int M, bool FEW>
+__global__ __launch_bounds__(kBlock) void k_corner(FeatArgs A) {
+  constexpr int Q = M / 4;
   const int64_t e = int64_t(blockIdx.x) * kBlock + threadIdx.x;
-  if (e >= nc * M) return;
-  const int64_t c = e / M;
-  const int ch = int(e % M);
-  float s = 0.0f;
-  for (int a = adj_off[c]; a < adj_off[c + 1]; ++a) s += vpart[int64_t(adj[a]) * M + ch];
-  dfeat[e] = s;
+  if (e >= A.corner_off[A.Lm] * Q) return;
+  const int64_t g = e / Q;
+  const int ch = int(e % Q) * 4;
+  const int l = level_of(A.corner_off, A.Lm, g);
+  const int64_t c = g - A.corner_off[l];
+  float4 s = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  const int32_t* adj = A.adj[l];
+  const int a0 = A.adj_off[l][c], a1 = A.adj_off[l][c + 1];
+  if constexpr (FEW) {
+    const int32_t* keys = A.rec_key + A.rec_off[l];
+    const float* recs = A.recs + A.rec_off[l] * 8 * M;
+    const int64_t nrec = A.rec_total[l];
+    const uint32_t* vfirst = A.vfirst + A.vox_off[l];
+    for (int a = a0; a < a1; ++a) {
+      const int v = adj[a] >> 3, j = adj[a] & 7;
+      const uint32_t first = vfirst[v];
+      if (first == 0) continue;
+      float4 t = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+      for (int64_t r = first - 1; r < nrec && keys[r] == v; ++r) {
+        const float4 x = *reinterpret_cast<const float4*>(recs + (r * 8 + j) * M + ch);
+        t.x += x.x, t.y += x.y, t.z += x.z, t.w += x.w;
+      }
+      s.x += t.x, s.y += t.y, s.z += t.z, s.w += t.w;
+    }
+  } else {
+    const float* vpart = A.vpart + A.vox_off[l] * 8 * M;
+    for (int a = a0; a < a1; ++a) {
+      const float4 x = *reinterpret_cast<const float4*>(vpart + int64_t(adj[a]) * M + ch);
+      s.x += x.x, s.y += x.y, s.z += x.z, s.w += x.w;
+    }
+  }
+  // the caller's gradient buffers need not be 16-byte aligned
+  float* d = A.dfeat[l] + c * M + ch;
+  d[0] = s.x, d[1] = s.y, d[2] = s.z, d[3] = s.w;
 }
 
 __global__ __launch_bounds__(kBlock) void k_zero(float* p, int64_t n) {
@@ -709,11 +875,14 @@ struct TrainWS {
   float* dec_part;
   float* dec_b2;
   uint32_t* rec_cnt;
+  int64_t cnt_stride;
   uint32_t* rec_total;
   int32_t* rec_key;
   float* recs;
   float* vpart;
-  int64_t maxrec;
+  uint32_t* vfirst;
+  int64_t rec_off[NGL_MAX_LODS + 1];  // records before each level
+  int64_t vox_off[NGL_MAX_LODS + 1];  // voxels before each level
   int64_t ntiles;
   size_t bytes;
 };
@@ -729,10 +898,13 @@ static TrainWS carve(const ngl_model& m, int64_t P, void* base) {
   };
   const int L = m.num_lods, M = m.feat_dim, H = m.hidden, din = M + (m.with_xyz ? 3 : 0);
   const int PH = H > 0 ? kBlock / H : 1;
-  int64_t nvmax = 0;
-  for (int l = 1; l <= L; ++l) nvmax = m.nvox[l + 1] > nvmax ? m.nvox[l + 1] : nvmax;
   w.ntiles = (P + kTile - 1) / kTile;
-  w.maxrec = nvmax + w.ntiles;
+  // a level has at most a record per voxel and per tile boundary, and per point
+  for (int l = 0; l < L; ++l) {
+    w.rec_off[l + 1] = w.rec_off[l] + std::min<int64_t>(m.nvox[l + 2] + w.ntiles, P);
+    w.vox_off[l + 1] = w.vox_off[l] + m.nvox[l + 2];
+  }
+  const bool few = P <= kRankSortMax;
   for (int k = 0; k < 2; ++k) {
     w.key[k] = reinterpret_cast<uint32_t*>(take(4 * size_t(P)));
     w.val[k] = reinterpret_cast<uint32_t*>(take(4 * size_t(P)));
@@ -742,14 +914,16 @@ static TrainWS carve(const ngl_model& m, int64_t P, void* base) {
   w.drows = reinterpret_cast<float*>(take(4 * size_t(L) * size_t(P) * size_t(M)));
   w.gs = reinterpret_cast<float*>(take(4 * size_t(L) * size_t(P)));
   w.vox_s = reinterpret_cast<int32_t*>(take(4 * size_t(L) * size_t(P)));
-  w.loss_part = reinterpret_cast<float*>(take(4 * size_t(P < kPointWaveMax ? P + 1 : (P + kBlock - 1) / kBlock + 1)));
+  w.loss_part = reinterpret_cast<float*>(take(4 * size_t(P < kPointWaveMax ? L * P + 1 : (P + kBlock - 1) / kBlock + 1)));
   w.dec_part = reinterpret_cast<float*>(take(4 * size_t(L) * kDecGrid * PH * size_t(H) * size_t(din + 2)));
   w.dec_b2 = reinterpret_cast<float*>(take(4 * size_t(L) * kDecGrid));
-  w.rec_cnt = reinterpret_cast<uint32_t*>(take(4 * size_t(w.ntiles + 1)));
-  w.rec_total = reinterpret_cast<uint32_t*>(take(4));
-  w.rec_key = reinterpret_cast<int32_t*>(take(4 * size_t(w.maxrec)));
-  w.recs = reinterpret_cast<float*>(take(4 * 8 * size_t(M) * size_t(w.maxrec)));
-  w.vpart = reinterpret_cast<float*>(take(4 * 8 * size_t(M) * size_t(nvmax)));
+  w.cnt_stride = (w.ntiles + 4) / 4 * 4;  // whole 16-byte vectors
+  w.rec_cnt = reinterpret_cast<uint32_t*>(take(4 * size_t(L) * size_t(w.cnt_stride)));
+  w.rec_total = reinterpret_cast<uint32_t*>(take(4 * size_t(L)));
+  w.rec_key = reinterpret_cast<int32_t*>(take(4 * size_t(w.rec_off[L])));
+  w.recs = reinterpret_cast<float*>(take(4 * 8 * size_t(M) * size_t(w.rec_off[L])));
+  w.vpart = reinterpret_cast<float*>(take(few ? 0 : 4 * 8 * size_t(M) * size_t(w.vox_off[L])));
+  w.vfirst = reinterpret_cast<uint32_t*>(take(few ? 4 * size_t(w.vox_off[L]) : 0));
   w.bytes = off;
   return w;
 }
@@ -776,16 +950,13 @@ static int run_train(const ngl_model& md, const float* x, const float* target, c
   const int D = Lm + 1;
   const unsigned pgrid = unsigned((P + kBlock - 1) / kBlock);
   // 1. sort by finest-cell Morton code (3D+1 key bits)
-  k_keys<<<pgrid, kBlock, 0, s>>>(x, P, D, w.key[0], w.val[0]);
-  const int bits = 3 * D + 1;
-  const int sgrid = sort_grid(P);
+  const bool few = P <= kRankSortMax;
   int cur = 0;
-  for (int shift = 0; shift < bits; shift += 8) {
-    k_radix_hist<<<sgrid, kBlock, 0, s>>>(w.key[cur], P, shift, w.hist);
-    k_scan_inplace<<<1, 1024, 0, s>>>(w.hist, int64_t(256) * sgrid, nullptr);
-    k_radix_scatter<<<sgrid, kBlock, 0, s>>>(w.key[cur], w.val[cur], w.key[cur ^ 1], w.val[cur ^ 1], P, shift,
-                                                 w.hist);
-    cur ^= 1;
+  if (few) {
+    k_rank_sort<<<unsigned((P + 63) / 64), kBlock, 0, s>>>(x, int(P), D, w.val[0], w.vfirst, w.vox_off[Lm]);
+  } else {
+    k_keys<<<pgrid, kBlock, 0, s>>>(x, P, D, w.key[0], w.val[0]);
+    cur = radix_sort_pairs(w.key, w.val, P, 3 * D + 1, sort_grid(P), w.hist, s);
   }
   const uint32_t* sidx = w.val[cur];
   // 2. per point
@@ -803,18 +974,22 @@ static int run_train(const ngl_model& md, const float* x, const float* target, c
   A.gs = w.gs;
   A.vox_s = w.vox_s;
   A.loss_part = w.loss_part;
+  int64_t nloss = 0;
   if (P < kPointWaveMax) {
-    // small batches: one wavefront per point
-    const unsigned wgrid = unsigned((P + kBlock / 64 - 1) / (kBlock / 64));
-    if (target) {
-      k_point_wave<M, XYZ, true><<<wgrid, kBlock, 0, s>>>(md, A);
-      if (loss) k_loss_reduce<<<1, kBlock, 0, s>>>(w.loss_part, int(P), 1.0f / float(P), loss);
-    } else {
-      k_point_wave<M, XYZ, false><<<wgrid, kBlock, 0, s>>>(md, A);
-    }
+    // small batches: one wavefront per point and LOD
+    const dim3 wgrid(unsigned((P + kBlock / 64 - 1) / (kBlock / 64)), unsigned(Lm));
+    const size_t lds = 4 * size_t(md.hidden) * size_t((M + (XYZ ? 3 : 0)) | 1);
+    nloss = target ? Lm * P : 0;
+    auto launch = [&](auto train) {
+      constexpr bool TRAIN = decltype(train)::value;
+      if (lds <= 49152) k_point_wave<M, XYZ, TRAIN, true><<<wgrid, kBlock, lds, s>>>(md, A);
+      else k_point_wave<M, XYZ, TRAIN, false><<<wgrid, kBlock, 0, s>>>(md, A);
+    };
+    if (target) launch(std::true_type{});
+    else launch(std::false_type{});
   } else if (target) {
     k_point<M, XYZ, true><<<pgrid, kBlock, 0, s>>>(md, A);
-    if (loss) k_loss_reduce<<<1, kBlock, 0, s>>>(w.loss_part, int(pgrid), 1.0f / float(P), loss);
+    nloss = pgrid;
   } else {
     k_point<M, XYZ, false><<<pgrid, kBlock, 0, s>>>(md, A);
   }
@@ -829,37 +1004,55 @@ static int run_train(const ngl_model& md, const float* x, const float* target, c
     O.dw2[l] = dw2[l];
   }
   O.db2 = db2;
+  O.loss = target ? loss : nullptr;
+  O.loss_part = w.loss_part;
+  O.nloss = nloss;
+  O.inv_p = 1.0f / float(P);
   const int din = M + (XYZ ? 3 : 0);
   const int H = md.hidden;
   const int waves = kBlock / 64;
-  k_dec_reduce<<<dim3(unsigned((H * (din + 2) + 1 + waves - 1) / waves), Lm), kBlock, 0, s>>>(
+  k_dec_reduce<<<dim3(unsigned((H * (din + 2) + 1 + waves - 1) / waves) + 1, Lm), kBlock, 0, s>>>(
       w.dec_part, w.dec_b2, H, din, kBlock / H, dgrid, O);
-  // 4. feature gradients, level by level
-  for (int l = 1; l <= Lm; ++l) {
-    const int64_t nc = md.ncorner[l - 1];
-    const int64_t nv = md.nvox[l + 1];
-    if (nc == 0) continue;
-    LevelArgs C{};
-    C.xs = x;
-    C.P = P;
-    C.lvl = l;
-    C.sidx = sidx;
-    C.vox_s = w.vox_s + int64_t(l - 1) * P;
-    C.drows = w.drows + int64_t(l - 1) * P * M;
-    C.rec_cnt = w.rec_cnt;
-    C.rec_total = w.rec_total;
-    C.rec_key = w.rec_key;
-    C.recs = w.recs;
-    C.maxrec = w.maxrec;
-    C.vpart = w.vpart;
-    k_rec_count<<<unsigned(w.ntiles), 64, 0, s>>>(C);
-    k_scan_inplace<<<1, 1024, 0, s>>>(w.rec_cnt, w.ntiles, w.rec_total);
-    if (P < kPointWaveMax) k_rec_write<M, true><<<unsigned(w.ntiles), 64, 0, s>>>(md, C);
-    else k_rec_write<M, false><<<unsigned(w.ntiles), 64, 0, s>>>(md, C);
-    k_vox_reduce<M><<<unsigned(nv), 64, 0, s>>>(C, nv);
-    k_corner<M><<<unsigned((nc * M + kBlock - 1) / kBlock), kBlock, 0, s>>>(md.corner_adj_off[l - 1],
-                                                                            md.corner_adj[l - 1], w.vpart, nc,
-                                                                            dfeat[l - 1]);
+  // 4. feature gradients
+  FeatArgs C{};
+  C.xs = x;
+  C.P = P;
+  C.Lm = Lm;
+  C.ntiles = w.ntiles;
+  C.sidx = sidx;
+  C.vox_s = w.vox_s;
+  C.drows = w.drows;
+  C.rec_cnt = w.rec_cnt;
+  C.cnt_stride = w.cnt_stride;
+  C.rec_total = w.rec_total;
+  C.rec_key = w.rec_key;
+  C.recs = w.recs;
+  C.vpart = w.vpart;
+  C.vfirst = w.vfirst;
+  for (int l = 0; l < Lm; ++l) {
+    C.rec_off[l + 1] = w.rec_off[l + 1];
+    C.vox_off[l + 1] = w.vox_off[l + 1];
+    C.corner_off[l + 1] = C.corner_off[l] + md.ncorner[l];
+    C.adj_off[l] = md.corner_adj_off[l];
+    C.adj[l] = md.corner_adj[l];
+    C.dfeat[l] = dfeat[l];
+  }
+  const dim3 tgrid(unsigned(w.ntiles), unsigned(Lm));
+  const unsigned cgrid = unsigned((C.corner_off[Lm] * (M / 4) + kBlock - 1) / kBlock);
+  if (cgrid == 0) {
+    NGL_LAUNCHED();
+    return NGL_OK;
+  }
+  if (few) {
+    k_rec_write<M, true, true><<<tgrid, 64, 0, s>>>(md, C);
+    k_corner<M, true><<<cgrid, kBlock, 0, s>>>(C);
+  } else {
+    k_rec_count<<<tgrid, 64, 0, s>>>(C);
+    k_scan_inplace<<<Lm, 1024, 0, s>>>(w.rec_cnt, w.ntiles, w.rec_total, w.cnt_stride);
+    if (P < kPointWaveMax) k_rec_write<M, true, false><<<tgrid, 64, 0, s>>>(md, C);
+    else k_rec_write<M, false, false><<<tgrid, 64, 0, s>>>(md, C);
+    k_vox_reduce<M><<<unsigned((C.vox_off[Lm] + kBlock / 64 - 1) / (kBlock / 64)), kBlock, 0, s>>>(C);
+    k_corner<M, false><<<cgrid, kBlock, 0, s>>>(C);
   }
   NGL_LAUNCHED();
   return NGL_OK;

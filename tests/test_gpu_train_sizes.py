@@ -1,0 +1,47 @@
+"""Gradients against the FP64 oracle where the training step changes its
+kernels: the largest batches of the rank sort (4,096 points) and of the
+wavefront-per-point stage (16,383), the ones after them, tile remainders,
+and a first decoder layer too large for the block's LDS.  The bar is the one
+of every gradient test: relative L2 and largest error 1e-4 per tensor."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2101_10994_amd import workloads as W
+
+from cases import make_case
+from test_gpu_train import compare, gpu_train, points
+
+pytestmark = pytest.mark.gpu
+
+
+MODELS = [(8, 32, False), (32, 128, True), (64, 256, True)]
+# One pre-activation of one point of this batch is closer to 0 than FP32
+# resolves, and the oracle takes the other side of that ReLU: one row of dW1
+# and db1 at LOD 3 and the rows of 8 corners differ, everything else agrees
+# to 2e-7.  (The kernels of 16,384 points, summing in another order, take the
+# oracle's side.)
+KINK = (64, 256, True, 16383)
+
+
+@pytest.mark.parametrize("m,H,xyz,P", [
+    pytest.param(*m, P, marks=pytest.mark.xfail(reason="a ReLU undetermined in FP32")) if (*m, P) == KINK else (*m, P)
+    for m in MODELS for P in (4095, 4096, 4097, 16383, 16384, 20_001)])
+def test_sizes(P, m, H, xyz):
+    case = make_case(W.tiny_shape(), 16, 3, m, H, sigma=0.1, with_xyz=xyz)
+    x, tgt = points(case, np.random.default_rng(P), P, 16)
+    compare(gpu_train(case, x, tgt), oracle.train_fwd_bwd(case.otree, case.oracle_model(), x, tgt))
+
+
+def test_one_voxel_and_points_outside():
+    """Every point of several tiles in one voxel (its records cross tiles),
+    and batches whose first or last points have no voxel."""
+    case = make_case(W.tiny_shape(), 16, 3, 8, 32, sigma=0.1)
+    rng = np.random.default_rng(3)
+    lo = -1.0 + case.ijk[7] * (2.0 / 16)
+    p = lo + rng.uniform(0.01, 0.115, (300, 3))
+    out = rng.uniform(1.1, 2.0, (70, 3))
+    for q in (p, np.concatenate([p, out]), np.concatenate([out, p[:1]])):
+        x = W.soa(q.astype(np.float32))
+        tgt = rng.normal(size=x.shape[1]).astype(np.float32)
+        compare(gpu_train(case, x, tgt), oracle.train_fwd_bwd(case.otree, case.oracle_model(), x, tgt))
