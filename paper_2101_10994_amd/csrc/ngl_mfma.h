@@ -344,7 +344,8 @@ __device__ inline void stage_rest32(float* stage, const float x[3]) {
   stage_rest32_row<M, XYZ>(stage, threadIdx.x & 63, x);
 }
 
-template <int M, bool XYZ>
+// NAN0: a NaN pre-activation counts as 0, as in the per-lane decoder.
+template <int M, bool XYZ, bool NAN0 = false>
 __device__ inline float tile_decode32(const float* frag, const float* w2s, const float* rows, int H) {
   using S = MfmaShape32<M, XYZ>;
   const int lane = threadIdx.x & 63;
@@ -352,6 +353,7 @@ __device__ inline float tile_decode32(const float* frag, const float* w2s, const
   float b[S::KS];
 #pragma unroll
   for (int s = 0; s < S::KS; ++s) b[s] = rows[j * S::ROW + 4 * s + g];
+  auto relu = [](float a) { return NAN0 ? fmaxf(a, 0.0f) : relu_bits(a); };
   float part = 0.0f;
   for (int h = 0; h < H / 16; ++h) {
     floatx4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -359,10 +361,10 @@ __device__ inline float tile_decode32(const float* frag, const float* w2s, const
     for (int s = 0; s < S::KS; ++s)
       acc = __builtin_amdgcn_mfma_f32_16x16x4f32(frag[(h * S::KS + s) * 64 + lane], b[s], acc, 0, 0, 0);
     const float4 w = *reinterpret_cast<const float4*>(w2s + 16 * h + 4 * g);
-    part = fmaf(w.x, relu_bits(acc[0]), part);
-    part = fmaf(w.y, relu_bits(acc[1]), part);
-    part = fmaf(w.z, relu_bits(acc[2]), part);
-    part = fmaf(w.w, relu_bits(acc[3]), part);
+    part = fmaf(w.x, relu(acc[0]), part);
+    part = fmaf(w.y, relu(acc[1]), part);
+    part = fmaf(w.z, relu(acc[2]), part);
+    part = fmaf(w.w, relu(acc[3]), part);
   }
   part += __shfl_xor(part, 16, 64);
   part += __shfl_xor(part, 32, 64);
@@ -453,6 +455,14 @@ struct DecF32 {
   }
   __device__ static float tile(const Frag* f, const float* w2s, const Stage* rows, int H) {
     return tile_decode32<M, XYZ>(f, w2s, rows, H);
+  }
+};
+
+// DecF32 for the all-LOD query (a row of blocks per LOD).
+template <int M, bool XYZ>
+struct DecF32All : DecF32<M, XYZ> {
+  __device__ static float tile(const float* f, const float* w2s, const float* rows, int H) {
+    return tile_decode32<M, XYZ, true>(f, w2s, rows, H);
   }
 };
 

