@@ -6,11 +6,14 @@
 //      the Morton code of their finest cell.  Canonical voxel indices are
 //      Morton ranks, so this order groups the points of every voxel of every
 //      level contiguously.
-//   2. k_point: per point (in sorted order) the level sum z_L, each decoder's
-//      forward pass, the upstream gradient g_L, dz_L = W1_z^T (g_L w2 . 1[a>0])
-//      and the suffix sums dpsi_l = sum_{L>=l} dz_L (Eq. 2 reversed).
-//   3. k_dec_grad / k_dec_reduce: decoder gradients as per-block partial sums
-//      over fixed point ranges, reduced in block order.
+//   2. per point (in sorted order) the level sum z_L, each decoder's forward
+//      pass, the upstream gradient g_L, dz_L = W1_z^T (g_L w2 . 1[a>0]) and the
+//      suffix sums dpsi_l = sum_{L>=l} dz_L (Eq. 2 reversed);
+//   3. decoder gradients as per-block partial sums over fixed point ranges,
+//      reduced in block order (k_dec_reduce).
+//      Large batches: k_point_sums, then k_dec_fused for all the rest of 2 and
+//      3.  Small ones: k_point_wave and k_dec_grad.  Widths that k_dec_fused
+//      does not take: k_point and k_dec_grad.
 //   4. all levels in one launch each: k_rec_count / scan / k_rec_write reduce
 //      fixed tiles of 64 sorted points into per-(voxel, tile) records of
 //      sum_p w_j(p) dpsi_l(p); k_vox_reduce sums each voxel's records; k_corner
@@ -23,12 +26,15 @@
 #include <cmath>
 #include <type_traits>
 #include "ngl_device.h"
+#include "ngl_mfma.h"
 #include "ngl_sort.h"
 
 namespace ngl {
 
 constexpr int kSortGrid = 256;  // most blocks of the radix-sort passes
 constexpr int kDecGrid = 204;   // most blocks per LOD of the decoder-gradient pass (5 LODs fill 256 CUs x 4)
+constexpr int kFusedWaves = 8;  // wavefronts per block of k_dec_fused
+constexpr int kFusedGrid = 512; // most blocks of k_dec_fused
 
 // Grids sized to the batch (small batches of the fitting loop would
 // otherwise pay for the full grids): at least 1024 keys per sort block and
@@ -125,6 +131,7 @@ struct PointArgs {
   float* gs;                // [L][P] g_L in sorted order
   int32_t* vox_s;           // [L][P] voxel per level in sorted order
   float* loss_part;         // [grid]
+  float* xsort[3];          // [P] each: the positions in sorted order (k_point_sums)
 };
 
 template <int M, bool XYZ, bool TRAIN>
@@ -430,6 +437,479 @@ __global__ __launch_bounds__(kBlock) void k_point_wave(ngl_model md, PointArgs A
   if (lane < M) A.drows[(int64_t(L - 1) * P + p) * M + lane] = d;
 }
 
+// ---------------------------------------------------------------------------
+// 2b. large batches: the point sums, then both passes of the decoders and
+// their gradients in one kernel on the matrix cores
+// ---------------------------------------------------------------------------
+// z_l of the sorted points, M / 8 lanes per point with 8 features each (a
+// row of 128 bytes is read by neighbouring lanes), in interp_level's order of
+// operations; also the voxels and the positions in sorted order.  Bound by
+// the random feature rows (8 per level and point).
+template <int M>
+__global__ __launch_bounds__(kBlock) void k_point_sums(ngl_model md, PointArgs A) {
+  constexpr int G = M / 8;
+  const int64_t e = int64_t(blockIdx.x) * kBlock + threadIdx.x;
+  const int64_t p = e / G, P = A.P;
+  const int sl = int(e % G);
+  if (p >= P) return;
+  const int64_t id = A.sidx[p];
+  const float x[3] = {A.xs[id], A.xs[P + id], A.xs[2 * P + id]};
+  if (sl == 0) {
+#pragma unroll
+    for (int i = 0; i < 3; ++i) A.xsort[i][p] = x[i];
+  }
+  const int Lm = md.num_lods;
+  int vox[NGL_MAX_LODS];
+  int cx = 0, cy = 0, cz = 0;
+  if (in_box(x[0], x[1], x[2])) {
+    const int r = 1 << (Lm + 1);
+    cx = cell_of(x[0], r);
+    cy = cell_of(x[1], r);
+    cz = cell_of(x[2], r);
+    descend<NGL_MAX_LODS>(md, cx, cy, cz, Lm + 1, vox);
+  } else {
+#pragma unroll
+    for (int l = 0; l < NGL_MAX_LODS; ++l) vox[l] = -1;
+  }
+  float z[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) z[i] = 0.0f;
+#pragma unroll
+  for (int l = 1; l <= NGL_MAX_LODS; ++l) {
+    if (l > Lm) break;
+    const int s = Lm - l, v = vox[l - 1];
+    if (v >= 0) {
+      float u[3];
+      cell_local(l, cx >> s, cy >> s, cz >> s, x, u);
+      const int4* cp = reinterpret_cast<const int4*>(md.corners[l - 1] + size_t(v) * 8);
+      const int4 c0 = cp[0], c1 = cp[1];
+      const int cs[8] = {c0.x, c0.y, c0.z, c0.w, c1.x, c1.y, c1.z, c1.w};
+      const float* feat = static_cast<const float*>(md.feat[l - 1]) + 8 * sl;
+      float4 f[8][2];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const float4* r = reinterpret_cast<const float4*>(feat + size_t(cs[j]) * M);
+        f[j][0] = r[0];
+        f[j][1] = r[1];
+      }
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const float wj = corner_weight(u, j);
+        const float fv[8] = {f[j][0].x, f[j][0].y, f[j][0].z, f[j][0].w, f[j][1].x, f[j][1].y, f[j][1].z, f[j][1].w};
+#pragma unroll
+        for (int i = 0; i < 8; ++i) z[i] = fmaf(wj, fv[i], z[i]);
+      }
+    }
+    if (sl == 0) A.vox_s[int64_t(l - 1) * P + p] = v;
+    float4* zr = reinterpret_cast<float4*>(A.zrows + (int64_t(l - 1) * P + p) * M + 8 * sl);
+    zr[0] = make_float4(z[0], z[1], z[2], z[3]);
+    zr[1] = make_float4(z[4], z[5], z[6], z[7]);
+  }
+}
+
+// Decoder passes of one wavefront tile of 16 points on v_mfma_f32_16x16x4f32
+// (FP32 operands, a chain of fmas over K), lane = (g = lane / 16, j = lane % 16):
+//   forward  a[16h + 4g + r] of point j from C = b1 and the inputs [x, z] in
+//            the order of the per-lane decoder: the same pre-activations bit
+//            for bit, so the same ReLUs;
+//   adjoint  dz = (w2 W1_z)^T (g 1[a > 0]), K-step (h, r) being the units
+//            {16h + 4g + r}, so that it takes the layout of the forward pass;
+//   G        += (g 1[a > 0]) [x, z, 1]^T over the points, transposed through
+//            LDS.  The position columns and the constant one take vector fmas
+//            instead of a third tile that would be three quarters padding.
+// dW1 = w2 G, db1 = w2 G_1 and, as a = W1 [x, z] + b1, dw2 = W1 G + b1 G_1:
+// no sums over g relu(a) are kept, which leaves registers for fragments read
+// ahead.  A wavefront runs its range of tiles for LOD after LOD from the
+// finest down and adds dpsi_{l+1}, which the same lane wrote, to dz_l.  The
+// block shares the decoder's fragments in LDS; each wavefront keeps its sums
+// in registers, which the block adds up in a fixed order after each LOD.
+// Bound by the matrix instructions, 200 of 32 cycles per tile and LOD at
+// M = 32, H = 128, and the vector ones beside them.  2^19 points, 5 LODs,
+// M = 32, H = 128: 764 us, and 140 for the sums before it, against 1040 us for
+// one lane per point (k_point) and 853 for the gradients (k_dec_grad).
+template <int M, bool XYZ, int HT>
+struct Fused {
+  static constexpr int OFF = XYZ ? 3 : 0;
+  static constexpr int DIN = M + OFF;
+  static constexpr int KS = (DIN + 3) / 4;     // K-steps of the forward pass
+  static constexpr int K4 = KS / 4;            // 16-byte fragments of four K-steps ...
+  static constexpr int K1 = KS % 4;            // ... and single ones
+  static constexpr int NT = M >= 16 ? M / 16 : 1;  // 16-wide tiles over the features
+  static constexpr int MT = M < 16 ? M : 16;   // features of a tile: NT * i + n, i < MT
+  static constexpr int H = 16 * HT;
+  static constexpr int W = DIN + 2;            // a row of the partial sums: dW1, db1, dw2
+  static constexpr int NW = kFusedWaves;
+  static constexpr int TR = 20;                // row of a transposed tile
+  // LDS, in floats
+  static constexpr int FW4 = 0;
+  static constexpr int FW1 = FW4 + HT * K4 * 256;
+  static constexpr int ADJ = FW1 + HT * K1 * 64;
+  static constexpr int B1 = ADJ + NT * HT * 256;
+  static constexpr int W2 = B1 + H;
+  static constexpr int TRB = W2 + H;           // [NW][HT][16][TR], and the sums after a LOD
+  static constexpr int ACC = HT * NT * 4;      // accumulators of W1_z per lane
+  static constexpr int SUM = (ACC + HT + 1) * 64;  // one wavefront's sums
+  static constexpr int TRN = NW * HT * 16 * TR > NW / 2 * SUM ? NW * HT * 16 * TR : NW / 2 * SUM;
+  static constexpr int FLOATS = TRB + TRN;
+};
+
+struct FusedArgs {
+  PointArgs A;
+  float* part;     // [L][slots][H][din+2]
+  float* part_b2;  // [L][kFusedGrid]
+  int64_t slots;   // of part per LOD
+};
+
+template <int M, bool XYZ, int HT>
+__global__ __launch_bounds__(64 * kFusedWaves) void k_dec_fused(ngl_model md, FusedArgs F) {
+  using S = Fused<M, XYZ, HT>;
+  constexpr int NT = S::NT, NW = S::NW, DIN = S::DIN, OFF = S::OFF, TR = S::TR;
+  __shared__ __align__(16) float sm[S::FLOATS];
+  const float4* fw4 = reinterpret_cast<const float4*>(sm + S::FW4);
+  const float* fw1 = sm + S::FW1;
+  const float4* adj = reinterpret_cast<const float4*>(sm + S::ADJ);
+  const float4* b1s = reinterpret_cast<const float4*>(sm + S::B1);
+  const float4* w2s = reinterpret_cast<const float4*>(sm + S::W2);
+  const PointArgs& A = F.A;
+  const int64_t P = A.P;
+  const int Lm = md.num_lods;
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // so tiles are uniform: scalar bases
+  float* tr = sm + S::TRB + w * (HT * 16 * TR);
+  const int64_t T = (P + 15) / 16, slots = int64_t(gridDim.x) * NW, me = int64_t(blockIdx.x) * NW + w;
+  const int t0 = int(T * me / slots), t1 = int(T * (me + 1) / slots);
+  // The three position arrays lie in one workspace.  Distances, so that a
+  // lane's choice between them stays arithmetic and is not made a load of the
+  // chosen pointer.
+  const float* X0 = A.xsort[0];
+  const int64_t dx1 = A.xsort[1] - X0, dx2 = A.xsort[2] - X0;
+  float loss = 0.0f;
+  for (int L = Lm; L >= 1; --L) {
+    // the decoder's fragments
+    {
+      int tid = threadIdx.x;
+      asm volatile("" : "+v"(tid));
+      cptr<float> W1 = as_const<float>(md.W1[L - 1]);
+      cptr<float> w2 = as_const<float>(md.w2[L - 1]);
+      float* s4 = sm + S::FW4;
+      for (int e = tid; e < HT * S::K4 * 256; e += 64 * NW) {
+        const int c = e & 3, ln = e >> 2 & 63, q = (e >> 8) % (S::K4 ? S::K4 : 1), h = (e >> 8) / (S::K4 ? S::K4 : 1);
+        const int k = 16 * q + 4 * c + (ln >> 4);
+        s4[e] = k < DIN ? W1[(16 * h + (ln & 15)) * DIN + k] : 0.0f;
+      }
+      for (int e = tid; e < HT * S::K1 * 64; e += 64 * NW) {
+        const int ln = e & 63, q = (e >> 6) % (S::K1 ? S::K1 : 1), h = (e >> 6) / (S::K1 ? S::K1 : 1);
+        const int k = 4 * (4 * S::K4 + q) + (ln >> 4);
+        sm[S::FW1 + e] = k < DIN ? W1[(16 * h + (ln & 15)) * DIN + k] : 0.0f;
+      }
+      for (int e = tid; e < NT * HT * 256; e += 64 * NW) {
+        const int r = e & 3, ln = e >> 2 & 63, h = (e >> 8) % HT, n = (e >> 8) / HT;
+        const int u = 16 * h + 4 * (ln >> 4) + r;
+        sm[S::ADJ + e] = (ln & 15) < S::MT
+                             ? w2[u] * W1[u * DIN + OFF + NT * (ln & 15) + n] : 0.0f;
+      }
+      for (int k = tid; k < S::H; k += 64 * NW) {
+        sm[S::B1 + k] = md.b1[L - 1][k];
+        sm[S::W2 + k] = md.w2[L - 1][k];
+      }
+    }
+    __syncthreads();
+    const float b2 = as_const<float>(md.b2)[L - 1];
+    const float lw = A.lod_w[L - 1];
+    const float* zl = A.zrows + int64_t(L - 1) * P * M;
+    float* dl = A.drows + int64_t(L - 1) * P * M;
+    const float* upl = A.target ? A.target : A.grad + int64_t(L - 1) * P;
+    floatx4 acc[HT][NT];  // G_z, units 16h + 4g + r, feature NT * j + n
+    float accx[HT][4];    // G_x and G_1, unit 16h + j, this lane's share of the points
+    float ab2 = 0.0f;
+#pragma unroll
+    for (int h = 0; h < HT; ++h) {
+#pragma unroll
+      for (int n = 0; n < NT; ++n) acc[h][n] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+      for (int r = 0; r < 4; ++r) accx[h][r] = 0.0f;
+    }
+    int g = lane >> 4, j = lane & 15;
+    // A tile's inputs 4s + g of point j and its target are requested while the
+    // tile before is in its backward pass (b is free then).
+    float b[S::KS], up = 0.0f;
+    uint32_t id = 0;
+    // point i of tile t from the tile's first: the last one past the batch
+    auto place = [&](int t, int i) { return min(i, int(min(P - 16 * int64_t(t), int64_t(16))) - 1); };
+    auto request = [&](int t) {
+      const int64_t p0 = 16 * int64_t(t);
+      const int jj = place(t, j);
+      up = upl[id];
+      const float* zt = zl + p0 * M;
+#pragma unroll
+      for (int s = 0; s < S::KS; ++s) {
+        const float* src = zt + jj * M + min(4 * s + g - OFF, M - 1);
+        if (OFF && s == 0) {
+          const int64_t dx = (g == 1 ? dx1 : 0) + (g == 2 ? dx2 : 0) + (g == 3 ? zl - X0 + p0 * (M - 1) + jj * (M - 1) : 0);
+          src = X0 + p0 + jj + dx;
+        }
+        b[s] = *src;
+      }
+    };
+    if (t0 < t1) {
+      id = (A.sidx + 16 * int64_t(t0))[place(t0, j)];
+      request(t0);
+    }
+#pragma unroll 1
+    for (int t = t0; t < t1; ++t) {
+      // addresses are formed anew for each tile: kept, they would take the
+      // registers of the sums
+      int ln = lane;
+      asm volatile("" : "+v"(ln));
+      g = ln >> 4, j = ln & 15;
+      const int64_t p0 = 16 * int64_t(t);
+      const bool live = p0 + j < P;
+      const int tn = t + 1 < t1 ? t + 1 : t;
+      const uint32_t idn = (A.sidx + 16 * int64_t(tn))[place(tn, j)];
+      // dpsi_{L+1}, features NT * (4g + r) + n: dz_L is accumulated on it
+      float u[4 * NT];
+      const int zoff = 4 * g < S::MT ? 4 * NT * g : 0;
+      {
+        const float4* u4 =
+            reinterpret_cast<const float4*>(A.drows + (int64_t(L < Lm ? L : L - 1) * P + p0) * M + place(t, j) * M + zoff);
+#pragma unroll
+        for (int q = 0; q < NT; ++q) {
+          const float4 v = u4[q];
+          u[4 * q] = v.x, u[4 * q + 1] = v.y, u[4 * q + 2] = v.z, u[4 * q + 3] = v.w;
+        }
+      }
+      if (4 * S::KS > DIN && g >= DIN % 4) b[S::KS - 1] = 0.0f;  // past the inputs
+      // forward, two chains of units at a time; in all three loops the next
+      // fragments are read before the current products
+      floatx4 a[HT];
+      float f[2][2][S::KS];
+      auto fetch = [&](int h) {
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          float* fe = f[h >> 1 & 1][e];
+#pragma unroll
+          for (int q = 0; q < S::K4; ++q) {
+            const float4 v = fw4[((h + e) * S::K4 + q) * 64 + ln];
+            fe[4 * q] = v.x, fe[4 * q + 1] = v.y, fe[4 * q + 2] = v.z, fe[4 * q + 3] = v.w;
+          }
+#pragma unroll
+          for (int q = 0; q < S::K1; ++q) fe[4 * S::K4 + q] = fw1[((h + e) * S::K1 + q) * 64 + ln];
+          const float4 c = b1s[4 * (h + e) + g];
+          a[h + e] = floatx4{c.x, c.y, c.z, c.w};
+        }
+      };
+      fetch(0);
+#pragma unroll
+      for (int h = 0; h < HT; h += 2) {
+        if (h + 2 < HT) fetch(h + 2);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int s = 0; s < S::KS; ++s)
+#pragma unroll
+          for (int e = 0; e < 2; ++e)
+            a[h + e] = __builtin_amdgcn_mfma_f32_16x16x4f32(f[h >> 1 & 1][e][s], b[s], a[h + e], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      // inputs of the points 4s + g: features NT * j + n, and the position
+      float zc[4][NT], xc[4][3];
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const int q = place(t, 4 * s + g);
+#pragma unroll
+        for (int n = 0; n < NT; ++n) zc[s][n] = (zl + p0 * M)[q * M + (M < 16 ? j & (M - 1) : NT * j + n)];
+        if constexpr (XYZ) xc[s][0] = (X0 + p0)[q], xc[s][1] = (X0 + dx1 + p0)[q], xc[s][2] = (X0 + dx2 + p0)[q];
+      }
+      float4 c2[2] = {w2s[g], w2s[4 + g]}, o = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+#pragma unroll
+      for (int h = 0; h < HT; ++h) {
+        const float4 c = c2[h & 1];
+        if (h + 2 < HT) c2[h & 1] = w2s[4 * (h + 2) + g];
+        o.x = fmaf(c.x, fmaxf(a[h][0], 0.0f), o.x);
+        o.y = fmaf(c.y, fmaxf(a[h][1], 0.0f), o.y);
+        o.z = fmaf(c.z, fmaxf(a[h][2], 0.0f), o.z);
+        o.w = fmaf(c.w, fmaxf(a[h][3], 0.0f), o.w);
+      }
+      float out = (o.x + o.y) + (o.z + o.w);
+      out += __shfl_xor(out, 16, 64);
+      out += __shfl_xor(out, 32, 64);
+      out += b2;
+      float gr = up;
+      if (A.target) {
+        const float wres = lw * (out - up);
+        loss = live && g == 0 ? fmaf(wres, out - up, loss) : loss;
+        gr = 2.0f * wres * A.inv_p;
+      }
+      gr = live ? gr : 0.0f;
+      ab2 += gr;
+      if (A.sdf_all && live && g == 0) (A.sdf_all + int64_t(L - 1) * P)[id] = out;
+      __builtin_amdgcn_sched_barrier(0);
+      id = idn;
+      request(tn);
+      // the ReLU's gradient times g, and the adjoint
+      floatx4 dz[NT];
+#pragma unroll
+      for (int i = 0; i < 4 * NT; ++i) asm volatile("" : "+v"(u[i]));  // requested above, not sunk below
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int n = 0; n < NT; ++n) dz[n][r] = L < Lm ? u[NT * r + n] : 0.0f;
+      float4 fa[2][NT];
+      auto fetch_adj = [&](int h) {
+#pragma unroll
+        for (int n = 0; n < NT; ++n) fa[h & 1][n] = adj[(n * HT + h) * 64 + ln];
+      };
+      fetch_adj(0);
+#pragma unroll
+      for (int h = 0; h < HT; ++h) {
+        if (h + 1 < HT) fetch_adj(h + 1);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) a[h][r] = a[h][r] > 0.0f ? gr : 0.0f;
+        *reinterpret_cast<float4*>(tr + (h * 16 + j) * TR + 4 * g) = make_float4(a[h][0], a[h][1], a[h][2], a[h][3]);
+        __builtin_amdgcn_sched_barrier(0);
+        const float4* fh = fa[h & 1];
+#pragma unroll
+        for (int n = 0; n < NT; ++n) dz[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(fh[n].x, a[h][0], dz[n], 0, 0, 0);
+#pragma unroll
+        for (int n = 0; n < NT; ++n) dz[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(fh[n].y, a[h][1], dz[n], 0, 0, 0);
+#pragma unroll
+        for (int n = 0; n < NT; ++n) dz[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(fh[n].z, a[h][2], dz[n], 0, 0, 0);
+#pragma unroll
+        for (int n = 0; n < NT; ++n) dz[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(fh[n].w, a[h][3], dz[n], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      // decoder gradients
+      wave_sync_lds();
+      float ga[2][4];
+      auto fetch_ga = [&](int h) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) ga[h & 1][s] = tr[(h * 16 + 4 * s + g) * TR + j];
+      };
+      fetch_ga(0);
+#pragma unroll
+      for (int h = 0; h < HT; ++h) {
+        if (h + 1 < HT) fetch_ga(h + 1);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          const float v = ga[h & 1][s];
+#pragma unroll
+          for (int n = 0; n < NT; ++n)
+            acc[h][n] = __builtin_amdgcn_mfma_f32_16x16x4f32(v, zc[s][n], acc[h][n], 0, 0, 0);
+#pragma unroll
+          for (int i = 0; i < OFF; ++i) accx[h][i] = fmaf(v, xc[s][i], accx[h][i]);
+          accx[h][3] += v;
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      wave_sync_lds();
+      if (live && 4 * g < S::MT) {
+        float4* d4 = reinterpret_cast<float4*>(dl + p0 * M + j * M + zoff);
+        float v[4 * NT];
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+          for (int n = 0; n < NT; ++n) v[NT * r + n] = dz[n][r];
+#pragma unroll
+        for (int q = 0; q < NT; ++q) d4[q] = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
+      }
+    }
+    // the wavefronts' sums, pairwise in a fixed order; px: column g (3: the
+    // bias) of unit 16h + j
+    int ln = lane;
+    asm volatile("" : "+v"(ln));
+    g = ln >> 4, j = ln & 15;
+    float px[HT];
+#pragma unroll
+    for (int h = 0; h < HT; ++h) {
+      // each exchange halves the values: a lane ends with the one it keeps
+      const float x0 = (g & 2 ? accx[h][2] : accx[h][0]) + __shfl_xor(g & 2 ? accx[h][0] : accx[h][2], 32, 64);
+      const float x1 = (g & 2 ? accx[h][3] : accx[h][1]) + __shfl_xor(g & 2 ? accx[h][1] : accx[h][3], 32, 64);
+      px[h] = (g & 1 ? x1 : x0) + __shfl_xor(g & 1 ? x0 : x1, 16, 64);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int off = 8; off >= 1; off >>= 1) ab2 += __shfl_xor(ab2, off, 64);
+    float* sums = sm + S::TRB;
+#pragma unroll 1
+    for (int half = NW / 2; half >= 1; half >>= 1) {
+      __syncthreads();  // the buffers are free
+      float* q = sums + (w & (half - 1)) * S::SUM + ln;
+      if (w >= half && w < 2 * half) {
+#pragma unroll
+        for (int h = 0; h < HT; ++h) {
+#pragma unroll
+          for (int n = 0; n < NT; ++n)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) q[((h * NT + n) * 4 + r) * 64] = acc[h][n][r];
+          q[(S::ACC + h) * 64] = px[h];
+        }
+        q[(S::ACC + HT) * 64] = ab2;
+      }
+      __syncthreads();
+      if (w < half) {
+#pragma unroll
+        for (int h = 0; h < HT; ++h) {
+#pragma unroll
+          for (int n = 0; n < NT; ++n)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[h][n][r] += q[((h * NT + n) * 4 + r) * 64];
+          px[h] += q[(S::ACC + h) * 64];
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        ab2 += q[(S::ACC + HT) * 64];
+      }
+    }
+    __syncthreads();
+    // wavefront 0 holds the block's sums: through LDS to whole lines
+    if (w == 0) {
+#pragma unroll
+      for (int h = 0; h < HT; ++h) {
+        float* row = sums + 16 * h * S::W;
+        if (j < S::MT) {
+#pragma unroll
+          for (int n = 0; n < NT; ++n)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) row[(4 * g + r) * S::W + OFF + NT * j + n] = acc[h][n][r];
+        }
+        if (OFF || g == 3) row[j * S::W + (g == 3 ? DIN : g)] = px[h];
+      }
+      if (lane == 0) F.part_b2[int64_t(L - 1) * kFusedGrid + blockIdx.x] = ab2;
+    }
+    __syncthreads();
+    // dw2 = W1 G_[x,z] + b1 G_1, from the forward pass's fragments
+    for (int k = threadIdx.x; k < S::H; k += 64 * NW) {
+      const int hk = k >> 4, uk = k & 15;
+      float* row = sums + k * S::W;
+      float d = sm[S::B1 + k] * row[DIN];
+#pragma unroll
+      for (int i = 0; i < DIN; ++i) {
+        const int at = uk + 16 * (i % 4);
+        const float wk = i < 16 * S::K4 ? sm[S::FW4 + ((hk * S::K4 + i / 16) * 64 + at) * 4 + i / 4 % 4]
+                                        : sm[S::FW1 + (hk * S::K1 + (i - 16 * S::K4) / 4) * 64 + at];
+        d = fmaf(wk, row[i], d);
+      }
+      row[DIN + 1] = d;
+    }
+    __syncthreads();
+    float* dst = F.part + ((L - 1) * F.slots + blockIdx.x) * (S::H * S::W);
+    for (int e = threadIdx.x; e < S::H * S::W; e += 64 * NW)
+      dst[e] = e % S::W <= DIN ? sums[e] * sm[S::W2 + e / S::W] : sums[e];
+    __syncthreads();
+  }
+  if (A.target) {
+#pragma unroll
+    for (int off = 8; off >= 1; off >>= 1) loss += __shfl_xor(loss, off, 64);
+    if (lane == 0) sm[S::TRB + w] = loss;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      float s = 0.0f;
+#pragma unroll
+      for (int i = 0; i < NW; ++i) s += sm[S::TRB + i];
+      A.loss_part[blockIdx.x] = s;
+    }
+  }
+}
+
 // *loss = inv_p * sum of part[0, n) in a fixed order, by the whole block.
 __device__ inline void loss_reduce(const float* part, int64_t n, float inv_p, float* loss) {
   __shared__ float sp[kBlock / 64];
@@ -457,7 +937,7 @@ struct DecArgs {
   const float* zrows;
   const float* gs;
   float* part;      // [L][kDecGrid][PH][H][din+2] (the first gridDim.x blocks)
-  float* part_b2;   // [L][kDecGrid]
+  float* part_b2;   // [L][kFusedGrid]
 };
 
 template <int M, bool XYZ>
@@ -532,7 +1012,7 @@ __global__ __launch_bounds__(kBlock) void k_dec_grad(ngl_model md, DecArgs A) {
   for (int i = 0; i < DIN; ++i) dst[i] = acc[i];
   dst[DIN] = ab1;
   dst[DIN + 1] = aw2;
-  if (threadIdx.x == 0) A.part_b2[int64_t(L - 1) * kDecGrid + blockIdx.x] = ab2;
+  if (threadIdx.x == 0) A.part_b2[int64_t(L - 1) * kFusedGrid + blockIdx.x] = ab2;
 }
 
 struct DecOut {
@@ -546,42 +1026,45 @@ struct DecOut {
   float inv_p;
 };
 
-// Each wavefront sums one output entry's nblk * PH partials: lane i takes
-// the partials i, i + 64, ... in order, then a fixed butterfly adds the
-// lanes (a fixed order, so the result is reproducible).  The extra
-// wavefront of block 0 sums db2.
-__global__ __launch_bounds__(kBlock) void k_dec_reduce(const float* __restrict__ part,
-                                                       const float* __restrict__ part_b2, int H, int din, int PH,
-                                                       int nblk, DecOut O) {
+// 64 entries of a LOD's sums per block, lane = entry, so that the partials are
+// read in whole lines: each wavefront adds the slots w, w + 4, ... in order and
+// the four are added in order (a fixed order, so the result is reproducible).
+// The block after the entries adds db2 and, at LOD 1, the loss.  256 slots of 5
+// LODs of the 128-unit decoder (24 MB) take under 10 us; a wavefront per entry,
+// its lanes a stride of 19 KB apart, took 49.
+__global__ __launch_bounds__(kBlock) void k_dec_reduce(const float* __restrict__ part, int64_t stride, int nslots,
+                                                       const float* __restrict__ part_b2, int nb2, int H, int din,
+                                                       DecOut O) {
   const int L = blockIdx.y + 1;
-  if (blockIdx.x == gridDim.x - 1) {  // the block after the entries
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  if (blockIdx.x == gridDim.x - 1) {
+    if (w == 0) {
+      float s = 0.0f;
+      for (int b = lane; b < nb2; b += 64) s += part_b2[int64_t(L - 1) * kFusedGrid + b];
+#pragma unroll
+      for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
+      if (lane == 0) O.db2[L - 1] = s;
+    }
     if (L == 1 && O.loss) loss_reduce(O.loss_part, O.nloss, O.inv_p, O.loss);
     return;
   }
-  const int lane = threadIdx.x & 63;
-  const int e = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);  // entry of [H][din+2]
+  __shared__ float sum[kBlock / 64][64];
   const int W = din + 2;
-  const int n = nblk * PH;
+  const int e = blockIdx.x * 64 + lane;  // entry of [H][din+2]
+  float s = 0.0f;
   if (e < H * W) {
+    const float* src = part + (L - 1) * stride * (H * W) + e;
+#pragma unroll 8
+    for (int j = w; j < nslots; j += kBlock / 64) s += src[int64_t(j) * (H * W)];
+  }
+  sum[w][lane] = s;
+  __syncthreads();
+  if (w == 0 && e < H * W) {
+    s = ((sum[0][lane] + sum[1][lane]) + sum[2][lane]) + sum[3][lane];
     const int k = e / W, i = e % W;
-    float s = 0.0f;
-    for (int j = lane; j < n; j += 64) {
-      const int b = j / PH, ph = j % PH;
-      s += part[(((int64_t(L - 1) * kDecGrid + b) * PH + ph) * H + k) * W + i];
-    }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
-    if (lane == 0) {
-      if (i < din) O.dW1[L - 1][k * din + i] = s;
-      else if (i == din) O.db1[L - 1][k] = s;
-      else O.dw2[L - 1][k] = s;
-    }
-  } else if (e == H * W) {
-    float s = 0.0f;
-    for (int b = lane; b < nblk; b += 64) s += part_b2[int64_t(L - 1) * kDecGrid + b];
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
-    if (lane == 0) O.db2[L - 1] = s;
+    if (i < din) O.dW1[L - 1][k * din + i] = s;
+    else if (i == din) O.db1[L - 1][k] = s;
+    else O.dw2[L - 1][k] = s;
   }
 }
 
@@ -914,9 +1397,10 @@ static TrainWS carve(const ngl_model& m, int64_t P, void* base) {
   w.drows = reinterpret_cast<float*>(take(4 * size_t(L) * size_t(P) * size_t(M)));
   w.gs = reinterpret_cast<float*>(take(4 * size_t(L) * size_t(P)));
   w.vox_s = reinterpret_cast<int32_t*>(take(4 * size_t(L) * size_t(P)));
-  w.loss_part = reinterpret_cast<float*>(take(4 * size_t(P < kPointWaveMax ? L * P + 1 : (P + kBlock - 1) / kBlock + 1)));
+  w.loss_part = reinterpret_cast<float*>(
+      take(4 * size_t(P < kPointWaveMax ? L * P + 1 : std::max<int64_t>((P + kBlock - 1) / kBlock + 1, kFusedGrid))));
   w.dec_part = reinterpret_cast<float*>(take(4 * size_t(L) * kDecGrid * PH * size_t(H) * size_t(din + 2)));
-  w.dec_b2 = reinterpret_cast<float*>(take(4 * size_t(L) * kDecGrid));
+  w.dec_b2 = reinterpret_cast<float*>(take(4 * size_t(L) * kFusedGrid));
   w.cnt_stride = (w.ntiles + 4) / 4 * 4;  // whole 16-byte vectors
   w.rec_cnt = reinterpret_cast<uint32_t*>(take(4 * size_t(L) * size_t(w.cnt_stride)));
   w.rec_total = reinterpret_cast<uint32_t*>(take(4 * size_t(L)));
@@ -940,6 +1424,29 @@ static int check_train(const ngl_model* m) {
     NGL_REQUIRE(m->ncorner[l - 1] == 0 || (m->corner_adj_off[l - 1] && (m->nvox[l + 1] == 0 || m->corner_adj[l - 1])),
                 "corner adjacency of level %d is null (needed for training)", l);
   return NGL_OK;
+}
+
+// Launches k_dec_fused with one round of resident blocks at most; returns the blocks.
+template <int M, bool XYZ, int HT>
+static int launch_fused_h(const ngl_model& md, const FusedArgs& F, hipStream_t s) {
+  const int threads = 64 * kFusedWaves;
+  int64_t grid = resident_grid(reinterpret_cast<const void*>(&k_dec_fused<M, XYZ, HT>), threads, 0, 0);
+  grid = std::min(grid, std::min<int64_t>(kFusedGrid, F.slots));
+  grid = std::min(grid, (F.A.P + 16 * kFusedWaves - 1) / (16 * kFusedWaves));
+  k_dec_fused<M, XYZ, HT><<<unsigned(grid), threads, 0, s>>>(md, F);
+  return int(grid);
+}
+
+template <int M, bool XYZ>
+static int launch_fused(const ngl_model& md, const FusedArgs& F, hipStream_t s) {
+  if constexpr (M <= 32) {
+    switch (md.hidden) {
+      case 32: return launch_fused_h<M, XYZ, 2>(md, F, s);
+      case 64: return launch_fused_h<M, XYZ, 4>(md, F, s);
+      default: return launch_fused_h<M, XYZ, 8>(md, F, s);
+    }
+  }
+  return 0;
 }
 
 template <int M, bool XYZ>
@@ -975,6 +1482,12 @@ static int run_train(const ngl_model& md, const float* x, const float* target, c
   A.vox_s = w.vox_s;
   A.loss_part = w.loss_part;
   int64_t nloss = 0;
+  const int PH = kBlock / md.hidden;
+  int nslots = 0, nb2 = 0;
+  // One fused kernel on the matrix cores where the batch fills the chip and a
+  // wavefront's registers hold a decoder's gradients: 65,537 points at M = 32,
+  // H = 128 take 185 us with the sums before it, 460 with a lane per point.
+  const bool fused = P >= kPointWaveMax && M <= 32 && (md.hidden == 32 || md.hidden == 64 || md.hidden == 128);
   if (P < kPointWaveMax) {
     // small batches: one wavefront per point and LOD
     const dim3 wgrid(unsigned((P + kBlock / 64 - 1) / (kBlock / 64)), unsigned(Lm));
@@ -987,6 +1500,15 @@ static int run_train(const ngl_model& md, const float* x, const float* target, c
     };
     if (target) launch(std::true_type{});
     else launch(std::false_type{});
+  } else if (fused) {
+    // key[0], key[1] and the other index array are free after the sort
+    A.xsort[0] = reinterpret_cast<float*>(w.key[0]);
+    A.xsort[1] = reinterpret_cast<float*>(w.key[1]);
+    A.xsort[2] = reinterpret_cast<float*>(w.val[1 - cur]);
+    k_point_sums<M><<<unsigned((P * (M / 8) + kBlock - 1) / kBlock), kBlock, 0, s>>>(md, A);
+    const FusedArgs B{A, w.dec_part, w.dec_b2, int64_t(kDecGrid) * PH};
+    nslots = nb2 = launch_fused<M, XYZ>(md, B, s);
+    nloss = target ? nb2 : 0;
   } else if (target) {
     k_point<M, XYZ, true><<<pgrid, kBlock, 0, s>>>(md, A);
     nloss = pgrid;
@@ -994,9 +1516,12 @@ static int run_train(const ngl_model& md, const float* x, const float* target, c
     k_point<M, XYZ, false><<<pgrid, kBlock, 0, s>>>(md, A);
   }
   // 3. decoder gradients
-  DecArgs B{x, P, sidx, w.zrows, w.gs, w.dec_part, w.dec_b2};
-  const int dgrid = dec_grid(P);
-  k_dec_grad<M, XYZ><<<dim3(dgrid, Lm), kBlock, 0, s>>>(md, B);
+  if (!fused) {
+    DecArgs B{x, P, sidx, w.zrows, w.gs, w.dec_part, w.dec_b2};
+    nb2 = dec_grid(P);
+    nslots = nb2 * PH;
+    k_dec_grad<M, XYZ><<<dim3(nb2, Lm), kBlock, 0, s>>>(md, B);
+  }
   DecOut O{};
   for (int l = 0; l < Lm; ++l) {
     O.dW1[l] = dW1[l];
@@ -1010,9 +1535,8 @@ static int run_train(const ngl_model& md, const float* x, const float* target, c
   O.inv_p = 1.0f / float(P);
   const int din = M + (XYZ ? 3 : 0);
   const int H = md.hidden;
-  const int waves = kBlock / 64;
-  k_dec_reduce<<<dim3(unsigned((H * (din + 2) + 1 + waves - 1) / waves) + 1, Lm), kBlock, 0, s>>>(
-      w.dec_part, w.dec_b2, H, din, kBlock / H, dgrid, O);
+  k_dec_reduce<<<dim3(unsigned((H * (din + 2) + 63) / 64) + 1, Lm), kBlock, 0, s>>>(
+      w.dec_part, int64_t(kDecGrid) * PH, nslots, w.dec_b2, nb2, H, din, O);
   // 4. feature gradients
   FeatArgs C{};
   C.xs = x;

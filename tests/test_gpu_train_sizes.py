@@ -45,3 +45,26 @@ def test_one_voxel_and_points_outside():
         x = W.soa(q.astype(np.float32))
         tgt = rng.normal(size=x.shape[1]).astype(np.float32)
         compare(gpu_train(case, x, tgt), oracle.train_fwd_bwd(case.otree, case.oracle_model(), x, tgt))
+
+
+# One ReLU of this batch again (one row of dW1 and db1 at LOD 3, 8 corners).
+KINK_FUSED = (32, 32, False, 16384)
+
+
+@pytest.mark.parametrize("m,H,xyz,P", [
+    pytest.param(*c, marks=pytest.mark.xfail(reason="a ReLU undetermined in FP32")) if c == KINK_FUSED else c
+    for c in [(m, H, xyz, P) for m in (8, 16, 32) for H in (32, 64, 128) for xyz in (True, False)
+              for P in (16384, 16391)]])
+def test_fused(m, H, xyz, P):
+    """Every width of the fused large-batch kernel, at whole tiles and at a
+    remainder.  Bars as above, but one ReLU that FP32 does not resolve may move
+    single feature rows (to 4e-4 of the largest in the batch noted above)."""
+    case = make_case(W.tiny_shape(), 16, 3, m, H, sigma=0.1, with_xyz=xyz)
+    x, tgt = points(case, np.random.default_rng(P + m), P, 16)
+    g, r = gpu_train(case, x, tgt), oracle.train_fwd_bwd(case.otree, case.oracle_model(), x, tgt)
+    assert abs(g["loss"] - r["loss"]) <= 1e-5 * abs(r["loss"])
+    for name in ("dfeat", "dW1", "db1", "dw2"):
+        for a, b in zip(g[name], r[name]):
+            assert np.linalg.norm(a - b) <= 1e-4 * np.linalg.norm(b), name
+            assert np.abs(a - b).max() <= (2e-3 if name == "dfeat" else 1e-4) * np.abs(b).max(), name
+    assert np.abs(g["db2"] - r["db2"]).max() <= 1e-4 * np.abs(r["db2"]).max()
