@@ -11,9 +11,9 @@
 //      suffix sums dpsi_l = sum_{L>=l} dz_L (Eq. 2 reversed);
 //   3. decoder gradients as per-block partial sums over fixed point ranges,
 //      reduced in block order (k_dec_reduce).
-//      Large batches: k_point_sums, then k_dec_fused for all the rest of 2 and
-//      3.  Small ones: k_point_wave and k_dec_grad.  Widths that k_dec_fused
-//      does not take: k_point and k_dec_grad.
+//      From kFusedMin points on: k_point_sums, then k_dec_fused for all the rest
+//      of 2 and 3.  Smaller batches, and widths that k_dec_fused does not take:
+//      k_point_wave or, from kPointWaveMax points on, k_point, and k_dec_grad.
 //   4. all levels in one launch each: k_rec_count / scan / k_rec_write reduce
 //      fixed tiles of 64 sorted points into per-(voxel, tile) records of
 //      sum_p w_j(p) dpsi_l(p); k_vox_reduce sums each voxel's records; k_corner
@@ -47,6 +47,19 @@ constexpr int kTile = 64;       // sorted points per record tile (one wavefront)
 // per point (k_point_wave): a lane per point would leave most of the chip
 // idle and each lane's serial decoder work would set the step time.
 constexpr int64_t kPointWaveMax = 16384;
+// From this many points on k_dec_fused takes the decoders of the widths it is
+// made for.  A step of 512 points, 5 LODs, M = 32, H = 128 takes 67 us with
+// k_point_wave and 68 with it, of 1,024 78 and 74, of 4,096 176 and 119, of
+// 16,383 403 and 161; at M = 8, H = 32 the two meet there as well.
+constexpr int64_t kFusedMin = 1024;
+// Up to this many points k_dec_fused gives each LOD a row of blocks instead of
+// having every block do all LODs in turn: a block's decoder is loaded and its
+// sums are added up once instead of for every LOD (14 us each time, against
+// 6 us per tile of a wavefront), and k_rec_write adds the LODs' rows, which up
+// to here mostly come from the caches: a step of 65,537 points takes 249 us
+// instead of 307, of 262,144 584 instead of 602, of 393,216 796 instead of 773.
+constexpr int64_t kFusedRowsMax = 262144;
+inline bool fused_rows(int64_t P) { return P <= kFusedRowsMax; }
 // Batches up to this many points are sorted by ranks in one launch
 // (k_rank_sort, P^2 comparisons on all keys in LDS, against ten radix
 // launches of one to four blocks), and each record tile counts the records
@@ -442,10 +455,12 @@ __global__ __launch_bounds__(kBlock) void k_point_wave(ngl_model md, PointArgs A
 // their gradients in one kernel on the matrix cores
 // ---------------------------------------------------------------------------
 // z_l of the sorted points, M / 8 lanes per point with 8 features each (a
-// row of 128 bytes is read by neighbouring lanes), in interp_level's order of
-// operations; also the voxels and the positions in sorted order.  Bound by
-// the random feature rows (8 per level and point).
-template <int M>
+// row of 128 bytes is read by neighbouring lanes); also the voxels and the
+// positions in sorted order.  A level's corners are added in interp_level's
+// order or, PAIRS, as k_point_wave adds them, so that a batch keeps the
+// pre-activations, and with them the ReLUs, of its size's per-point kernel bit
+// for bit.  Bound by the random feature rows (8 per level and point).
+template <int M, bool PAIRS>
 __global__ __launch_bounds__(kBlock) void k_point_sums(ngl_model md, PointArgs A) {
   constexpr int G = M / 8;
   const int64_t e = int64_t(blockIdx.x) * kBlock + threadIdx.x;
@@ -492,12 +507,24 @@ __global__ __launch_bounds__(kBlock) void k_point_sums(ngl_model md, PointArgs A
         f[j][0] = r[0];
         f[j][1] = r[1];
       }
+      if constexpr (PAIRS) {
+        float wj[8];
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const float wj = corner_weight(u, j);
-        const float fv[8] = {f[j][0].x, f[j][0].y, f[j][0].z, f[j][0].w, f[j][1].x, f[j][1].y, f[j][1].z, f[j][1].w};
+        for (int j = 0; j < 8; ++j) wj[j] = corner_weight(u, j);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) z[i] = fmaf(wj, fv[i], z[i]);
+        for (int i = 0; i < 8; ++i) {
+          auto fv = [&](int j) { return reinterpret_cast<const float*>(&f[j][i / 4])[i % 4]; };
+          auto pair = [&](int j) { return fmaf(wj[j], fv(j), wj[j + 1] * fv(j + 1)); };
+          z[i] += (pair(0) + pair(2)) + (pair(4) + pair(6));
+        }
+      } else {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const float wj = corner_weight(u, j);
+          const float fv[8] = {f[j][0].x, f[j][0].y, f[j][0].z, f[j][0].w, f[j][1].x, f[j][1].y, f[j][1].z, f[j][1].w};
+#pragma unroll
+          for (int i = 0; i < 8; ++i) z[i] = fmaf(wj, fv[i], z[i]);
+        }
       }
     }
     if (sl == 0) A.vox_s[int64_t(l - 1) * P + p] = v;
@@ -507,26 +534,35 @@ __global__ __launch_bounds__(kBlock) void k_point_sums(ngl_model md, PointArgs A
   }
 }
 
-// Decoder passes of one wavefront tile of 16 points on v_mfma_f32_16x16x4f32
-// (FP32 operands, a chain of fmas over K), lane = (g = lane / 16, j = lane % 16):
-//   forward  a[16h + 4g + r] of point j from C = b1 and the inputs [x, z] in
-//            the order of the per-lane decoder: the same pre-activations bit
-//            for bit, so the same ReLUs;
-//   adjoint  dz = (w2 W1_z)^T (g 1[a > 0]), K-step (h, r) being the units
-//            {16h + 4g + r}, so that it takes the layout of the forward pass;
-//   G        += (g 1[a > 0]) [x, z, 1]^T over the points, transposed through
-//            LDS.  The position columns and the constant one take vector fmas
-//            instead of a third tile that would be three quarters padding.
-// dW1 = w2 G, db1 = w2 G_1 and, as a = W1 [x, z] + b1, dw2 = W1 G + b1 G_1:
-// no sums over g relu(a) are kept, which leaves registers for fragments read
-// ahead.  A wavefront runs its range of tiles for LOD after LOD from the
-// finest down and adds dpsi_{l+1}, which the same lane wrote, to dz_l.  The
-// block shares the decoder's fragments in LDS; each wavefront keeps its sums
-// in registers, which the block adds up in a fixed order after each LOD.
-// Bound by the matrix instructions, 200 of 32 cycles per tile and LOD at
-// M = 32, H = 128, and the vector ones beside them.  2^19 points, 5 LODs,
-// M = 32, H = 128: 764 us, and 140 for the sums before it, against 1040 us for
-// one lane per point (k_point) and 853 for the gradients (k_dec_grad).
+// Decoder passes of a wavefront's tiles of 16 points, two at a time; lane =
+// (g = lane / 16, j = lane % 16):
+//   forward  a[16h + 4g + r] of point j on v_mfma_f32_16x16x4f32 (a chain of
+//            fmas over K) from C = b1 and the inputs [x, z] in the order of
+//            the per-lane decoder: the same pre-activations bit for bit, so the
+//            same ReLUs;
+//   adjoint  dz = g (w2 W1_z)^T 1[a > 0];
+//   G        = sum over the points of 1[a > 0] (g [x, z, 1])^T.
+// In the last two one factor is a mask, which BF16 holds exactly, and the
+// other is the sum of three BF16 parts (8 + 8 + 8 bits, all of FP32's; a fourth
+// holds what w2 W1 has beyond them, an error that all points would share), so
+// v_mfma_f32_16x16x32_bf16 forms the exact products and adds them in FP32 at a
+// fifth of the time of the FP32 instruction.  The masks are kept as bits: of
+// point j's units for the adjoint, and through LDS of a unit's points for G;
+// their BF16 value is 2, which is one bit, against g / 2.
+// As a = W1 [x, z] + b1, dw2 = W1 G + b1 G_1; dW1 = w2 G and db1 = w2 G_1 are
+// left to k_dec_reduce.
+// A wavefront runs its range of tiles for LOD after LOD from the finest down
+// and adds dpsi_{l+1}, which the same lane wrote, to dz_l.  The block shares
+// the decoder's fragments in LDS; each wavefront keeps its sums in registers,
+// which the block adds up in a fixed order after each LOD.
+// Bound by the matrix instructions (2304 cycles per tile and LOD forward, 960
+// for the rest at M = 32, H = 128) and about as much vector work beside the
+// FP32 ones, which does not overlap with them.  2^19 points, 5 LODs, M = 32,
+// H = 128: 569 us (764 with FP32 matrix instructions throughout), and 141 for
+// the sums before it, against 1040 us for one lane per point (k_point) and 853
+// for the gradients (k_dec_grad).  Errors against FP64, median over four widths
+// and eight sizes: feature gradients 6.2e-8 (6.3e-8 before), dW1 4.6e-8 (5.1e-8),
+// dw2 3.7e-8 (4.2e-8).
 template <int M, bool XYZ, int HT>
 struct Fused {
   static constexpr int OFF = XYZ ? 3 : 0;
@@ -536,21 +572,23 @@ struct Fused {
   static constexpr int K1 = KS % 4;            // ... and single ones
   static constexpr int NT = M >= 16 ? M / 16 : 1;  // 16-wide tiles over the features
   static constexpr int MT = M < 16 ? M : 16;   // features of a tile: NT * i + n, i < MT
+  static constexpr int CT = M < 16 ? 1 : NT + 1;   // tiles of G: features, and position and constant from
+  static constexpr int X0 = M < 16 ? M : 0;        // column X0 of the last one on
   static constexpr int H = 16 * HT;
+  static constexpr int HP = HT / 2;            // K-steps of the adjoint
   static constexpr int W = DIN + 2;            // a row of the partial sums: dW1, db1, dw2
   static constexpr int NW = kFusedWaves;
-  static constexpr int TR = 20;                // row of a transposed tile
+  static constexpr int WS = 160;               // scratch of a wavefront: masks [2][4][16], g [2][16]
   // LDS, in floats
   static constexpr int FW4 = 0;
   static constexpr int FW1 = FW4 + HT * K4 * 256;
-  static constexpr int ADJ = FW1 + HT * K1 * 64;
-  static constexpr int B1 = ADJ + NT * HT * 256;
+  static constexpr int ADJ = FW1 + HT * K1 * 64;   // [4][NT][HP][64] fragments of 8 BF16
+  static constexpr int B1 = ADJ + 4 * NT * HP * 256;
   static constexpr int W2 = B1 + H;
-  static constexpr int TRB = W2 + H;           // [NW][HT][16][TR], and the sums after a LOD
-  static constexpr int ACC = HT * NT * 4;      // accumulators of W1_z per lane
-  static constexpr int SUM = (ACC + HT + 1) * 64;  // one wavefront's sums
-  static constexpr int TRN = NW * HT * 16 * TR > NW / 2 * SUM ? NW * HT * 16 * TR : NW / 2 * SUM;
-  static constexpr int FLOATS = TRB + TRN;
+  static constexpr int TRB = W2 + H;           // the scratch, and the sums after a LOD
+  static constexpr int ACC = HT * CT * 4;      // accumulators of G per lane
+  static constexpr int SUM = (ACC + 1) * 64;   // one wavefront's sums
+  static constexpr int FLOATS = TRB + std::max({NW * WS, NW / 2 * SUM, H * W});
 };
 
 struct FusedArgs {
@@ -560,14 +598,25 @@ struct FusedArgs {
   int64_t slots;   // of part per LOD
 };
 
+// base[off], off in bytes: a scalar base and a 32-bit vector offset.
+template <typename T>
+__device__ inline T at32(const void* base, uint32_t off) {
+  return *reinterpret_cast<const T*>(static_cast<const char*>(base) + off);
+}
+
+// Bits i and i + 16 of v as a pair of BF16 values, 2 or 0 (i < 16).
+__device__ inline uint32_t mask2(uint32_t v, int i) {
+  return (i <= 14 ? v << (14 - i) : v >> (i - 14)) & 0x40004000u;
+}
+
 template <int M, bool XYZ, int HT>
 __global__ __launch_bounds__(64 * kFusedWaves) void k_dec_fused(ngl_model md, FusedArgs F) {
   using S = Fused<M, XYZ, HT>;
-  constexpr int NT = S::NT, NW = S::NW, DIN = S::DIN, OFF = S::OFF, TR = S::TR;
+  constexpr int NT = S::NT, CT = S::CT, NW = S::NW, DIN = S::DIN, OFF = S::OFF;
   __shared__ __align__(16) float sm[S::FLOATS];
   const float4* fw4 = reinterpret_cast<const float4*>(sm + S::FW4);
   const float* fw1 = sm + S::FW1;
-  const float4* adj = reinterpret_cast<const float4*>(sm + S::ADJ);
+  const uint4* adj = reinterpret_cast<const uint4*>(sm + S::ADJ);
   const float4* b1s = reinterpret_cast<const float4*>(sm + S::B1);
   const float4* w2s = reinterpret_cast<const float4*>(sm + S::W2);
   const PointArgs& A = F.A;
@@ -575,7 +624,8 @@ __global__ __launch_bounds__(64 * kFusedWaves) void k_dec_fused(ngl_model md, Fu
   const int Lm = md.num_lods;
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // so tiles are uniform: scalar bases
-  float* tr = sm + S::TRB + w * (HT * 16 * TR);
+  uint32_t* mw = reinterpret_cast<uint32_t*>(sm + S::TRB + w * S::WS);
+  float* gw = sm + S::TRB + w * S::WS + 128;
   const int64_t T = (P + 15) / 16, slots = int64_t(gridDim.x) * NW, me = int64_t(blockIdx.x) * NW + w;
   const int t0 = int(T * me / slots), t1 = int(T * (me + 1) / slots);
   // The three position arrays lie in one workspace.  Distances, so that a
@@ -584,7 +634,12 @@ __global__ __launch_bounds__(64 * kFusedWaves) void k_dec_fused(ngl_model md, Fu
   const float* X0 = A.xsort[0];
   const int64_t dx1 = A.xsort[1] - X0, dx2 = A.xsort[2] - X0;
   float loss = 0.0f;
-  for (int L = Lm; L >= 1; --L) {
+  // a row of blocks per LOD (which leaves the sum over the LODs to k_rec_write),
+  // or all of them in turn
+  const bool rows = gridDim.y > 1;
+  const int first = rows ? Lm - int(blockIdx.y) : Lm, last = rows ? first : 1;
+  for (int L = first; L >= last; --L) {
+    const bool above = !rows && L < Lm;  // dpsi_{L+1} is there
     // the decoder's fragments
     {
       int tid = threadIdx.x;
@@ -602,11 +657,19 @@ __global__ __launch_bounds__(64 * kFusedWaves) void k_dec_fused(ngl_model md, Fu
         const int k = 4 * (4 * S::K4 + q) + (ln >> 4);
         sm[S::FW1 + e] = k < DIN ? W1[(16 * h + (ln & 15)) * DIN + k] : 0.0f;
       }
-      for (int e = tid; e < NT * HT * 256; e += 64 * NW) {
-        const int r = e & 3, ln = e >> 2 & 63, h = (e >> 8) % HT, n = (e >> 8) / HT;
-        const int u = 16 * h + 4 * (ln >> 4) + r;
-        sm[S::ADJ + e] = (ln & 15) < S::MT
-                             ? w2[u] * W1[u * DIN + OFF + NT * (ln & 15) + n] : 0.0f;
+      for (int e = tid; e < NT * S::HP * 512; e += 64 * NW) {
+        const int c = e & 7, ln = e >> 3 & 63, hp = (e >> 9) % S::HP, n = (e >> 9) / S::HP;
+        const int u = 32 * hp + 16 * (c >> 2) + 4 * (ln >> 4) + (c & 3);
+        const float f1 = w2[u], f2 = (ln & 15) < S::MT ? W1[u * DIN + OFF + NT * (ln & 15) + n] : 0.0f;
+        float v = f1 * f2;
+        uint16_t* dst = reinterpret_cast<uint16_t*>(sm + S::ADJ) + e;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const uint32_t t = f32_to_bf16_bits(v);
+          dst[q * NT * S::HP * 512] = uint16_t(t);
+          const float part = __uint_as_float(t << 16);
+          v = q == 0 ? fmaf(f1, f2, -part) : v - part;  // of the exact product
+        }
       }
       for (int k = tid; k < S::H; k += 64 * NW) {
         sm[S::B1 + k] = md.b1[L - 1][k];
@@ -619,214 +682,257 @@ __global__ __launch_bounds__(64 * kFusedWaves) void k_dec_fused(ngl_model md, Fu
     const float* zl = A.zrows + int64_t(L - 1) * P * M;
     float* dl = A.drows + int64_t(L - 1) * P * M;
     const float* upl = A.target ? A.target : A.grad + int64_t(L - 1) * P;
-    floatx4 acc[HT][NT];  // G_z, units 16h + 4g + r, feature NT * j + n
-    float accx[HT][4];    // G_x and G_1, unit 16h + j, this lane's share of the points
+    floatx4 acc[HT][CT];  // G, units 16h + 4g + r, column j of each tile
     float ab2 = 0.0f;
 #pragma unroll
-    for (int h = 0; h < HT; ++h) {
+    for (int h = 0; h < HT; ++h)
 #pragma unroll
-      for (int n = 0; n < NT; ++n) acc[h][n] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-      for (int r = 0; r < 4; ++r) accx[h][r] = 0.0f;
-    }
+      for (int n = 0; n < CT; ++n) acc[h][n] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
     int g = lane >> 4, j = lane & 15;
     // A tile's inputs 4s + g of point j and its target are requested while the
     // tile before is in its backward pass (b is free then).
-    float b[S::KS], up = 0.0f;
-    uint32_t id = 0;
+    float b[2][S::KS], up[2] = {0.0f, 0.0f};
+    uint32_t id[2] = {0, 0};
     // point i of tile t from the tile's first: the last one past the batch
-    auto place = [&](int t, int i) { return min(i, int(min(P - 16 * int64_t(t), int64_t(16))) - 1); };
-    auto request = [&](int t) {
+    auto place = [&](int t, int i) {
+      return uint32_t(min(i, int(min(P - 16 * int64_t(t), int64_t(16))) - 1));
+    };
+    auto request = [&](int t, int q) {
       const int64_t p0 = 16 * int64_t(t);
-      const int jj = place(t, j);
-      up = upl[id];
+      const uint32_t jj = place(t, j);
+      up[q] = upl[id[q]];
       const float* zt = zl + p0 * M;
 #pragma unroll
       for (int s = 0; s < S::KS; ++s) {
-        const float* src = zt + jj * M + min(4 * s + g - OFF, M - 1);
         if (OFF && s == 0) {
-          const int64_t dx = (g == 1 ? dx1 : 0) + (g == 2 ? dx2 : 0) + (g == 3 ? zl - X0 + p0 * (M - 1) + jj * (M - 1) : 0);
-          src = X0 + p0 + jj + dx;
+          const int64_t dx = (g == 1 ? dx1 : 0) + (g == 2 ? dx2 : 0) + (g == 3 ? zl - X0 + (p0 + jj) * (M - 1) : 0);
+          b[q][s] = (X0 + p0 + jj)[dx];
+        } else {
+          b[q][s] = at32<float>(zt, 4 * (jj * M + min(4 * s + g - OFF, M - 1)));
         }
-        b[s] = *src;
       }
     };
+    auto second = [&](int t) { return t + 1 < t1 ? t + 1 : t; };
     if (t0 < t1) {
-      id = (A.sidx + 16 * int64_t(t0))[place(t0, j)];
-      request(t0);
+      id[0] = (A.sidx + 16 * int64_t(t0))[place(t0, j)];
+      id[1] = (A.sidx + 16 * int64_t(second(t0)))[place(second(t0), j)];
+      request(t0, 0);
+      request(second(t0), 1);
     }
 #pragma unroll 1
-    for (int t = t0; t < t1; ++t) {
+    for (int t = t0; t < t1; t += 2) {
       // addresses are formed anew for each tile: kept, they would take the
       // registers of the sums
       int ln = lane;
       asm volatile("" : "+v"(ln));
       g = ln >> 4, j = ln & 15;
-      const int64_t p0 = 16 * int64_t(t);
-      const bool live = p0 + j < P;
-      const int tn = t + 1 < t1 ? t + 1 : t;
-      const uint32_t idn = (A.sidx + 16 * int64_t(tn))[place(tn, j)];
-      // dpsi_{L+1}, features NT * (4g + r) + n: dz_L is accumulated on it
-      float u[4 * NT];
-      const int zoff = 4 * g < S::MT ? 4 * NT * g : 0;
-      {
-        const float4* u4 =
-            reinterpret_cast<const float4*>(A.drows + (int64_t(L < Lm ? L : L - 1) * P + p0) * M + place(t, j) * M + zoff);
+      const int tn = t + 2 < t1 ? t + 2 : t;
 #pragma unroll
-        for (int q = 0; q < NT; ++q) {
-          const float4 v = u4[q];
-          u[4 * q] = v.x, u[4 * q + 1] = v.y, u[4 * q + 2] = v.z, u[4 * q + 3] = v.w;
+      for (int q = 0; q < 2; ++q) {
+        const int tq = t + q;
+        if (q == 1 && tq >= t1) {  // no second tile: no unit is on
+          mw[64 + ln] = 0u;
+          if (g == 0) gw[16 + j] = 0.0f;
+          break;
         }
-      }
-      if (4 * S::KS > DIN && g >= DIN % 4) b[S::KS - 1] = 0.0f;  // past the inputs
-      // forward, two chains of units at a time; in all three loops the next
-      // fragments are read before the current products
-      floatx4 a[HT];
-      float f[2][2][S::KS];
-      auto fetch = [&](int h) {
+        const int64_t p0 = 16 * int64_t(tq);
+        const bool live = p0 + j < P;
+        const int tnq = q ? second(tn) : tn;
+        const uint32_t idn = (A.sidx + 16 * int64_t(tnq))[place(tnq, j)];
+        // dpsi_{L+1}, features NT * (4g + r) + n
+        float u[4 * NT];
+        const uint32_t zoff = 4 * g < S::MT ? 4 * NT * g : 0;
+        {
+          const float* ul = A.drows + (int64_t(above ? L : L - 1) * P + p0) * M;
 #pragma unroll
-        for (int e = 0; e < 2; ++e) {
-          float* fe = f[h >> 1 & 1][e];
-#pragma unroll
-          for (int q = 0; q < S::K4; ++q) {
-            const float4 v = fw4[((h + e) * S::K4 + q) * 64 + ln];
-            fe[4 * q] = v.x, fe[4 * q + 1] = v.y, fe[4 * q + 2] = v.z, fe[4 * q + 3] = v.w;
+          for (int e = 0; e < NT; ++e) {
+            const float4 v = at32<float4>(ul, 4 * (place(tq, j) * M + zoff) + 16 * e);
+            u[4 * e] = v.x, u[4 * e + 1] = v.y, u[4 * e + 2] = v.z, u[4 * e + 3] = v.w;
           }
-#pragma unroll
-          for (int q = 0; q < S::K1; ++q) fe[4 * S::K4 + q] = fw1[((h + e) * S::K1 + q) * 64 + ln];
-          const float4 c = b1s[4 * (h + e) + g];
-          a[h + e] = floatx4{c.x, c.y, c.z, c.w};
         }
-      };
-      fetch(0);
+        if (4 * S::KS > DIN && g >= DIN % 4) b[q][S::KS - 1] = 0.0f;  // past the inputs
+        // forward, two chains of units at a time; the next fragments are read
+        // before the current products
+        floatx4 a[HT];
+        float f[2][2][S::KS];
+        auto fetch = [&](int h) {
 #pragma unroll
-      for (int h = 0; h < HT; h += 2) {
-        if (h + 2 < HT) fetch(h + 2);
-        __builtin_amdgcn_sched_barrier(0);
+          for (int e = 0; e < 2; ++e) {
+            float* fe = f[h >> 1 & 1][e];
 #pragma unroll
-        for (int s = 0; s < S::KS; ++s)
+            for (int k = 0; k < S::K4; ++k) {
+              const float4 v = fw4[((h + e) * S::K4 + k) * 64 + ln];
+              fe[4 * k] = v.x, fe[4 * k + 1] = v.y, fe[4 * k + 2] = v.z, fe[4 * k + 3] = v.w;
+            }
 #pragma unroll
-          for (int e = 0; e < 2; ++e)
-            a[h + e] = __builtin_amdgcn_mfma_f32_16x16x4f32(f[h >> 1 & 1][e][s], b[s], a[h + e], 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      // inputs of the points 4s + g: features NT * j + n, and the position
-      float zc[4][NT], xc[4][3];
+            for (int k = 0; k < S::K1; ++k) fe[4 * S::K4 + k] = fw1[((h + e) * S::K1 + k) * 64 + ln];
+            const float4 c = b1s[4 * (h + e) + g];
+            a[h + e] = floatx4{c.x, c.y, c.z, c.w};
+          }
+        };
+        fetch(0);
 #pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const int q = place(t, 4 * s + g);
+        for (int h = 0; h < HT; h += 2) {
+          if (h + 2 < HT) fetch(h + 2);
+          __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int n = 0; n < NT; ++n) zc[s][n] = (zl + p0 * M)[q * M + (M < 16 ? j & (M - 1) : NT * j + n)];
-        if constexpr (XYZ) xc[s][0] = (X0 + p0)[q], xc[s][1] = (X0 + dx1 + p0)[q], xc[s][2] = (X0 + dx2 + p0)[q];
-      }
-      float4 c2[2] = {w2s[g], w2s[4 + g]}, o = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+          for (int s = 0; s < S::KS; ++s)
 #pragma unroll
-      for (int h = 0; h < HT; ++h) {
-        const float4 c = c2[h & 1];
-        if (h + 2 < HT) c2[h & 1] = w2s[4 * (h + 2) + g];
-        o.x = fmaf(c.x, fmaxf(a[h][0], 0.0f), o.x);
-        o.y = fmaf(c.y, fmaxf(a[h][1], 0.0f), o.y);
-        o.z = fmaf(c.z, fmaxf(a[h][2], 0.0f), o.z);
-        o.w = fmaf(c.w, fmaxf(a[h][3], 0.0f), o.w);
-      }
-      float out = (o.x + o.y) + (o.z + o.w);
-      out += __shfl_xor(out, 16, 64);
-      out += __shfl_xor(out, 32, 64);
-      out += b2;
-      float gr = up;
-      if (A.target) {
-        const float wres = lw * (out - up);
-        loss = live && g == 0 ? fmaf(wres, out - up, loss) : loss;
-        gr = 2.0f * wres * A.inv_p;
-      }
-      gr = live ? gr : 0.0f;
-      ab2 += gr;
-      if (A.sdf_all && live && g == 0) (A.sdf_all + int64_t(L - 1) * P)[id] = out;
-      __builtin_amdgcn_sched_barrier(0);
-      id = idn;
-      request(tn);
-      // the ReLU's gradient times g, and the adjoint
-      floatx4 dz[NT];
-#pragma unroll
-      for (int i = 0; i < 4 * NT; ++i) asm volatile("" : "+v"(u[i]));  // requested above, not sunk below
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int n = 0; n < NT; ++n) dz[n][r] = L < Lm ? u[NT * r + n] : 0.0f;
-      float4 fa[2][NT];
-      auto fetch_adj = [&](int h) {
-#pragma unroll
-        for (int n = 0; n < NT; ++n) fa[h & 1][n] = adj[(n * HT + h) * 64 + ln];
-      };
-      fetch_adj(0);
-#pragma unroll
-      for (int h = 0; h < HT; ++h) {
-        if (h + 1 < HT) fetch_adj(h + 1);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) a[h][r] = a[h][r] > 0.0f ? gr : 0.0f;
-        *reinterpret_cast<float4*>(tr + (h * 16 + j) * TR + 4 * g) = make_float4(a[h][0], a[h][1], a[h][2], a[h][3]);
-        __builtin_amdgcn_sched_barrier(0);
-        const float4* fh = fa[h & 1];
-#pragma unroll
-        for (int n = 0; n < NT; ++n) dz[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(fh[n].x, a[h][0], dz[n], 0, 0, 0);
-#pragma unroll
-        for (int n = 0; n < NT; ++n) dz[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(fh[n].y, a[h][1], dz[n], 0, 0, 0);
-#pragma unroll
-        for (int n = 0; n < NT; ++n) dz[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(fh[n].z, a[h][2], dz[n], 0, 0, 0);
-#pragma unroll
-        for (int n = 0; n < NT; ++n) dz[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(fh[n].w, a[h][3], dz[n], 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      // decoder gradients
-      wave_sync_lds();
-      float ga[2][4];
-      auto fetch_ga = [&](int h) {
-#pragma unroll
-        for (int s = 0; s < 4; ++s) ga[h & 1][s] = tr[(h * 16 + 4 * s + g) * TR + j];
-      };
-      fetch_ga(0);
-#pragma unroll
-      for (int h = 0; h < HT; ++h) {
-        if (h + 1 < HT) fetch_ga(h + 1);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-          const float v = ga[h & 1][s];
-#pragma unroll
-          for (int n = 0; n < NT; ++n)
-            acc[h][n] = __builtin_amdgcn_mfma_f32_16x16x4f32(v, zc[s][n], acc[h][n], 0, 0, 0);
-#pragma unroll
-          for (int i = 0; i < OFF; ++i) accx[h][i] = fmaf(v, xc[s][i], accx[h][i]);
-          accx[h][3] += v;
+            for (int e = 0; e < 2; ++e)
+              a[h + e] = __builtin_amdgcn_mfma_f32_16x16x4f32(f[h >> 1 & 1][e][s], b[q][s], a[h + e], 0, 0, 0);
+          __builtin_amdgcn_sched_barrier(0);
         }
+        // the output, and the ReLUs that are on: bit 2h + r / 2 + 16 (r % 2) is
+        // unit 16h + 4g + r
+        float4 c2[2] = {w2s[4 * (HT - 1) + g], w2s[4 * (HT - 2) + g]}, o = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        uint32_t even = 0, odd = 0;
+#pragma unroll
+        for (int i = 0; i < HT; ++i) {
+          const int h = HT - 1 - i;
+          const float4 c = c2[i & 1];
+          if (h >= 2) c2[i & 1] = w2s[4 * (h - 2) + g];
+          even = even + even + (a[h][2] > 0.0f ? 1u : 0u);
+          odd = odd + odd + (a[h][3] > 0.0f ? 1u : 0u);
+          even = even + even + (a[h][0] > 0.0f ? 1u : 0u);
+          odd = odd + odd + (a[h][1] > 0.0f ? 1u : 0u);
+          o.x = fmaf(c.x, fmaxf(a[h][0], 0.0f), o.x);
+          o.y = fmaf(c.y, fmaxf(a[h][1], 0.0f), o.y);
+          o.z = fmaf(c.z, fmaxf(a[h][2], 0.0f), o.z);
+          o.w = fmaf(c.w, fmaxf(a[h][3], 0.0f), o.w);
+        }
+        const uint32_t on = even | odd << 16;
+        float out = (o.x + o.y) + (o.z + o.w);
+        out += __shfl_xor(out, 16, 64);
+        out += __shfl_xor(out, 32, 64);
+        out += b2;
+        float gr = up[q];
+        if (A.target) {
+          const float wres = lw * (out - up[q]);
+          loss = live && g == 0 ? fmaf(wres, out - up[q], loss) : loss;
+          gr = 2.0f * wres * A.inv_p;
+        }
+        gr = live ? gr : 0.0f;
+        ab2 += gr;
+        if (A.sdf_all && live && g == 0) (A.sdf_all + int64_t(L - 1) * P)[id[q]] = out;
+        gr *= 0.5f;  // the masks' BF16 value is 2
+        mw[64 * q + ln] = on;
+        if (g == 0) gw[16 * q + j] = gr;
         __builtin_amdgcn_sched_barrier(0);
+        id[q] = idn;
+        request(tnq, q);
+        // adjoint: the first parts' sum d1 is mostly exact (8-bit numbers), the
+        // others' d2 small, so that dz is rounded about once
+        floatx4 d1[NT], d2[NT];
+#pragma unroll
+        for (int n = 0; n < NT; ++n) d1[n] = d2[n] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int hp = 0; hp < S::HP; ++hp) {
+          const bf16x8 m = __builtin_bit_cast(
+              bf16x8, make_uint4(mask2(on, 4 * hp), mask2(on, 4 * hp + 1), mask2(on, 4 * hp + 2), mask2(on, 4 * hp + 3)));
+#pragma unroll
+          for (int e = 3; e >= 0; --e)
+#pragma unroll
+            for (int n = 0; n < NT; ++n) {
+              const bf16x8 wf = __builtin_bit_cast(bf16x8, adj[((e * NT + n) * S::HP + hp) * 64 + ln]);
+              floatx4& d = e ? d2[n] : d1[n];
+              d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf, m, d, 0, 0, 0);
+            }
+        }
+        if (live && 4 * g < S::MT) {
+          float4* d4 = reinterpret_cast<float4*>(dl + p0 * M + j * M + zoff);
+          float v[4 * NT];
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int n = 0; n < NT; ++n) v[NT * r + n] = fmaf(gr, d1[n][r], gr * d2[n][r]) + (above ? u[NT * r + n] : 0.0f);
+#pragma unroll
+          for (int e = 0; e < NT; ++e) d4[e] = make_float4(v[4 * e], v[4 * e + 1], v[4 * e + 2], v[4 * e + 3]);
+        }
+      }
+      // G: the columns' values of the points 4g + e of both tiles
+      float zc[2][4][CT];
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const int64_t p0 = 16 * int64_t(q ? second(t) : t);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const uint32_t pe = place(q ? second(t) : t, 4 * g + e);
+          if constexpr (M >= 16) {
+#pragma unroll
+            for (int n = 0; n < NT; ++n) zc[q][e][n] = at32<float>(zl + p0 * M, 4 * (pe * M + NT * j + n));
+          }
+          // the last tile: position and constant from column X0 on
+          const int c = j - S::X0;
+          if constexpr (M < 16 || XYZ) {
+            const int64_t dx = (c == 1 ? dx1 : 0) + (c == 2 ? dx2 : 0) + (c < 0 ? zl - X0 + (p0 + pe) * (M - 1) + j : 0);
+            zc[q][e][CT - 1] = (X0 + p0 + pe)[dx];
+          }
+        }
       }
       wave_sync_lds();
-      if (live && 4 * g < S::MT) {
-        float4* d4 = reinterpret_cast<float4*>(dl + p0 * M + j * M + zoff);
-        float v[4 * NT];
+      uint4 y[CT][3];  // g times them, in three BF16 parts
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
+      for (int q = 0; q < 2; ++q) {
+        const float4 gv = *reinterpret_cast<const float4*>(gw + 16 * q + 4 * g);
+        const float gp[4] = {gv.x, gv.y, gv.z, gv.w};
 #pragma unroll
-          for (int n = 0; n < NT; ++n) v[NT * r + n] = dz[n][r];
+        for (int n = 0; n < CT; ++n) {
 #pragma unroll
-        for (int q = 0; q < NT; ++q) d4[q] = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
+          for (int e = 0; e < 4; e += 2) {
+            float v0 = zc[q][e][n], v1 = zc[q][e + 1][n];
+            if (n == CT - 1) {
+              const int c = j - S::X0;
+              const bool one = c == 3, none = c > 3 || (!XYZ && c >= 0 && c < 3);
+              v0 = one ? 1.0f : none ? 0.0f : v0;
+              v1 = one ? 1.0f : none ? 0.0f : v1;
+            }
+            const float z0 = v0, z1 = v1;
+            v0 *= gp[e];
+            v1 *= gp[e + 1];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+              const uint32_t t2 = pack_bf16(v0, v1);
+              const float part0 = __uint_as_float(t2 << 16), part1 = __uint_as_float(t2 & 0xffff0000u);
+              v0 = k == 0 ? fmaf(z0, gp[e], -part0) : v0 - part0;  // of the exact products
+              v1 = k == 0 ? fmaf(z1, gp[e + 1], -part1) : v1 - part1;
+              if (q == 0 && e == 0) y[n][k].x = t2;
+              if (q == 0 && e == 2) y[n][k].y = t2;
+              if (q == 1 && e == 0) y[n][k].z = t2;
+              if (q == 1 && e == 2) y[n][k].w = t2;
+            }
+          }
+        }
       }
+      // unit 16h + j of the points 4g + e: bit 2h of the low half after the shift
+      uint32_t mp[4];
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const uint4 v = *reinterpret_cast<const uint4*>(mw + 64 * q + 16 * (j >> 2) + 4 * g);
+        const int sh = (j >> 1 & 1) + 16 * (j & 1);
+        mp[2 * q] = __builtin_amdgcn_perm(v.y >> sh, v.x >> sh, 0x05040100u);
+        mp[2 * q + 1] = __builtin_amdgcn_perm(v.w >> sh, v.z >> sh, 0x05040100u);
+      }
+#pragma unroll
+      for (int h = 0; h < HT; ++h) {
+        const uint4 m = make_uint4(mask2(mp[0], 2 * h), mask2(mp[1], 2 * h), mask2(mp[2], 2 * h), mask2(mp[3], 2 * h));
+        floatx4 d[CT];
+#pragma unroll
+        for (int n = 0; n < CT; ++n) d[n] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int e = 2; e >= 0; --e)
+#pragma unroll
+          for (int n = 0; n < CT; ++n)
+            d[n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, m),
+                                                           __builtin_bit_cast(bf16x8, y[n][e]), d[n], 0, 0, 0);
+#pragma unroll
+        for (int n = 0; n < CT; ++n) acc[h][n] += d[n];
+      }
+      wave_sync_lds();
     }
-    // the wavefronts' sums, pairwise in a fixed order; px: column g (3: the
-    // bias) of unit 16h + j
+    // the wavefronts' sums, pairwise in a fixed order
     int ln = lane;
     asm volatile("" : "+v"(ln));
     g = ln >> 4, j = ln & 15;
-    float px[HT];
-#pragma unroll
-    for (int h = 0; h < HT; ++h) {
-      // each exchange halves the values: a lane ends with the one it keeps
-      const float x0 = (g & 2 ? accx[h][2] : accx[h][0]) + __shfl_xor(g & 2 ? accx[h][0] : accx[h][2], 32, 64);
-      const float x1 = (g & 2 ? accx[h][3] : accx[h][1]) + __shfl_xor(g & 2 ? accx[h][1] : accx[h][3], 32, 64);
-      px[h] = (g & 1 ? x1 : x0) + __shfl_xor(g & 1 ? x0 : x1, 16, 64);
-      __builtin_amdgcn_sched_barrier(0);
-    }
 #pragma unroll
     for (int off = 8; off >= 1; off >>= 1) ab2 += __shfl_xor(ab2, off, 64);
     float* sums = sm + S::TRB;
@@ -838,25 +944,23 @@ __global__ __launch_bounds__(64 * kFusedWaves) void k_dec_fused(ngl_model md, Fu
 #pragma unroll
         for (int h = 0; h < HT; ++h) {
 #pragma unroll
-          for (int n = 0; n < NT; ++n)
+          for (int n = 0; n < CT; ++n)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) q[((h * NT + n) * 4 + r) * 64] = acc[h][n][r];
-          q[(S::ACC + h) * 64] = px[h];
+            for (int r = 0; r < 4; ++r) q[((h * CT + n) * 4 + r) * 64] = acc[h][n][r];
         }
-        q[(S::ACC + HT) * 64] = ab2;
+        q[S::ACC * 64] = ab2;
       }
       __syncthreads();
       if (w < half) {
 #pragma unroll
         for (int h = 0; h < HT; ++h) {
 #pragma unroll
-          for (int n = 0; n < NT; ++n)
+          for (int n = 0; n < CT; ++n)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) acc[h][n][r] += q[((h * NT + n) * 4 + r) * 64];
-          px[h] += q[(S::ACC + h) * 64];
+            for (int r = 0; r < 4; ++r) acc[h][n][r] += q[((h * CT + n) * 4 + r) * 64];
           __builtin_amdgcn_sched_barrier(0);
         }
-        ab2 += q[(S::ACC + HT) * 64];
+        ab2 += q[S::ACC * 64];
       }
     }
     __syncthreads();
@@ -865,13 +969,16 @@ __global__ __launch_bounds__(64 * kFusedWaves) void k_dec_fused(ngl_model md, Fu
 #pragma unroll
       for (int h = 0; h < HT; ++h) {
         float* row = sums + 16 * h * S::W;
-        if (j < S::MT) {
 #pragma unroll
-          for (int n = 0; n < NT; ++n)
+        for (int n = 0; n < CT; ++n) {
+          // the entry's column, or none
+          const int c = j - S::X0;
+          const int col = n < CT - 1 || c < 0 ? OFF + NT * j + n : c < OFF ? c : c == 3 ? DIN : -1;
+          if (col >= 0) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r) row[(4 * g + r) * S::W + OFF + NT * j + n] = acc[h][n][r];
+            for (int r = 0; r < 4; ++r) row[(4 * g + r) * S::W + col] = acc[h][n][r];
+          }
         }
-        if (OFF || g == 3) row[j * S::W + (g == 3 ? DIN : g)] = px[h];
       }
       if (lane == 0) F.part_b2[int64_t(L - 1) * kFusedGrid + blockIdx.x] = ab2;
     }
@@ -880,20 +987,19 @@ __global__ __launch_bounds__(64 * kFusedWaves) void k_dec_fused(ngl_model md, Fu
     for (int k = threadIdx.x; k < S::H; k += 64 * NW) {
       const int hk = k >> 4, uk = k & 15;
       float* row = sums + k * S::W;
-      float d = sm[S::B1 + k] * row[DIN];
+      double d = double(sm[S::B1 + k]) * row[DIN];  // may cancel
 #pragma unroll
       for (int i = 0; i < DIN; ++i) {
         const int at = uk + 16 * (i % 4);
         const float wk = i < 16 * S::K4 ? sm[S::FW4 + ((hk * S::K4 + i / 16) * 64 + at) * 4 + i / 4 % 4]
                                         : sm[S::FW1 + (hk * S::K1 + (i - 16 * S::K4) / 4) * 64 + at];
-        d = fmaf(wk, row[i], d);
+        d = fma(double(wk), double(row[i]), d);
       }
-      row[DIN + 1] = d;
+      row[DIN + 1] = float(d);
     }
     __syncthreads();
     float* dst = F.part + ((L - 1) * F.slots + blockIdx.x) * (S::H * S::W);
-    for (int e = threadIdx.x; e < S::H * S::W; e += 64 * NW)
-      dst[e] = e % S::W <= DIN ? sums[e] * sm[S::W2 + e / S::W] : sums[e];
+    for (int e = threadIdx.x; e < S::H * S::W; e += 64 * NW) dst[e] = sums[e];
     __syncthreads();
   }
   if (A.target) {
@@ -905,7 +1011,7 @@ __global__ __launch_bounds__(64 * kFusedWaves) void k_dec_fused(ngl_model md, Fu
       float s = 0.0f;
 #pragma unroll
       for (int i = 0; i < NW; ++i) s += sm[S::TRB + i];
-      A.loss_part[blockIdx.x] = s;
+      A.loss_part[blockIdx.y * gridDim.x + blockIdx.x] = s;
     }
   }
 }
@@ -1019,6 +1125,7 @@ struct DecOut {
   float* dW1[NGL_MAX_LODS];
   float* db1[NGL_MAX_LODS];
   float* dw2[NGL_MAX_LODS];
+  const float* w2[NGL_MAX_LODS];  // factor of dW1 and db1, or null
   float* db2;
   float* loss;             // nullable: the sum of loss_part[0, nloss) times inv_p
   const float* loss_part;
@@ -1052,16 +1159,23 @@ __global__ __launch_bounds__(kBlock) void k_dec_reduce(const float* __restrict__
   const int W = din + 2;
   const int e = blockIdx.x * 64 + lane;  // entry of [H][din+2]
   float s = 0.0f;
-  if (e < H * W) {
+  if (e < H * W) {  // eight sums of every 32nd slot, then pairwise: short chains
     const float* src = part + (L - 1) * stride * (H * W) + e;
-#pragma unroll 8
-    for (int j = w; j < nslots; j += kBlock / 64) s += src[int64_t(j) * (H * W)];
+    float q[8] = {};
+    int j = w;
+    for (; j + 28 < nslots; j += 32)
+#pragma unroll
+      for (int i = 0; i < 8; ++i) q[i] += src[int64_t(j + 4 * i) * (H * W)];
+    for (; j < nslots; j += 4) q[0] += src[int64_t(j) * (H * W)];
+    s = ((q[0] + q[1]) + (q[2] + q[3])) + ((q[4] + q[5]) + (q[6] + q[7]));
   }
   sum[w][lane] = s;
   __syncthreads();
   if (w == 0 && e < H * W) {
-    s = ((sum[0][lane] + sum[1][lane]) + sum[2][lane]) + sum[3][lane];
+    double t = ((double(sum[0][lane]) + sum[1][lane]) + sum[2][lane]) + sum[3][lane];
     const int k = e / W, i = e % W;
+    if (O.w2[L - 1] && i <= din) t *= O.w2[L - 1][k];
+    s = float(t);
     if (i < din) O.dW1[L - 1][k * din + i] = s;
     else if (i == din) O.db1[L - 1][k] = s;
     else O.dw2[L - 1][k] = s;
@@ -1426,14 +1540,16 @@ static int check_train(const ngl_model* m) {
   return NGL_OK;
 }
 
-// Launches k_dec_fused with one round of resident blocks at most; returns the blocks.
+// Launches k_dec_fused with one round of resident blocks at most; returns the
+// blocks per LOD.
 template <int M, bool XYZ, int HT>
 static int launch_fused_h(const ngl_model& md, const FusedArgs& F, hipStream_t s) {
   const int threads = 64 * kFusedWaves;
   int64_t grid = resident_grid(reinterpret_cast<const void*>(&k_dec_fused<M, XYZ, HT>), threads, 0, 0);
   grid = std::min(grid, std::min<int64_t>(kFusedGrid, F.slots));
-  grid = std::min(grid, (F.A.P + 16 * kFusedWaves - 1) / (16 * kFusedWaves));
-  k_dec_fused<M, XYZ, HT><<<unsigned(grid), threads, 0, s>>>(md, F);
+  const int rows = fused_rows(F.A.P) ? md.num_lods : 1;
+  grid = std::max<int64_t>(1, std::min(grid / rows, (F.A.P + 16 * kFusedWaves - 1) / (16 * kFusedWaves)));
+  k_dec_fused<M, XYZ, HT><<<dim3(unsigned(grid), unsigned(rows)), threads, 0, s>>>(md, F);
   return int(grid);
 }
 
@@ -1484,11 +1600,10 @@ static int run_train(const ngl_model& md, const float* x, const float* target, c
   int64_t nloss = 0;
   const int PH = kBlock / md.hidden;
   int nslots = 0, nb2 = 0;
-  // One fused kernel on the matrix cores where the batch fills the chip and a
-  // wavefront's registers hold a decoder's gradients: 65,537 points at M = 32,
-  // H = 128 take 185 us with the sums before it, 460 with a lane per point.
-  const bool fused = P >= kPointWaveMax && M <= 32 && (md.hidden == 32 || md.hidden == 64 || md.hidden == 128);
-  if (P < kPointWaveMax) {
+  // one fused kernel on the matrix cores where a wavefront's registers hold a
+  // decoder's gradients
+  const bool fused = P >= kFusedMin && M <= 32 && (md.hidden == 32 || md.hidden == 64 || md.hidden == 128);
+  if (!fused && P < kPointWaveMax) {
     // small batches: one wavefront per point and LOD
     const dim3 wgrid(unsigned((P + kBlock / 64 - 1) / (kBlock / 64)), unsigned(Lm));
     const size_t lds = 4 * size_t(md.hidden) * size_t((M + (XYZ ? 3 : 0)) | 1);
@@ -1505,10 +1620,12 @@ static int run_train(const ngl_model& md, const float* x, const float* target, c
     A.xsort[0] = reinterpret_cast<float*>(w.key[0]);
     A.xsort[1] = reinterpret_cast<float*>(w.key[1]);
     A.xsort[2] = reinterpret_cast<float*>(w.val[1 - cur]);
-    k_point_sums<M><<<unsigned((P * (M / 8) + kBlock - 1) / kBlock), kBlock, 0, s>>>(md, A);
+    const unsigned sgrid = unsigned((P * (M / 8) + kBlock - 1) / kBlock);
+    if (P < kPointWaveMax) k_point_sums<M, true><<<sgrid, kBlock, 0, s>>>(md, A);
+    else k_point_sums<M, false><<<sgrid, kBlock, 0, s>>>(md, A);
     const FusedArgs B{A, w.dec_part, w.dec_b2, int64_t(kDecGrid) * PH};
     nslots = nb2 = launch_fused<M, XYZ>(md, B, s);
-    nloss = target ? nb2 : 0;
+    nloss = target ? nb2 * (fused_rows(P) ? Lm : 1) : 0;
   } else if (target) {
     k_point<M, XYZ, true><<<pgrid, kBlock, 0, s>>>(md, A);
     nloss = pgrid;
@@ -1527,6 +1644,7 @@ static int run_train(const ngl_model& md, const float* x, const float* target, c
     O.dW1[l] = dW1[l];
     O.db1[l] = db1[l];
     O.dw2[l] = dw2[l];
+    O.w2[l] = fused ? static_cast<const float*>(md.w2[l]) : nullptr;
   }
   O.db2 = db2;
   O.loss = target ? loss : nullptr;
@@ -1573,7 +1691,7 @@ static int run_train(const ngl_model& md, const float* x, const float* target, c
   } else {
     k_rec_count<<<tgrid, 64, 0, s>>>(C);
     k_scan_inplace<<<Lm, 1024, 0, s>>>(w.rec_cnt, w.ntiles, w.rec_total, w.cnt_stride);
-    if (P < kPointWaveMax) k_rec_write<M, true, false><<<tgrid, 64, 0, s>>>(md, C);
+    if (P < kPointWaveMax || (fused && fused_rows(P))) k_rec_write<M, true, false><<<tgrid, 64, 0, s>>>(md, C);
     else k_rec_write<M, false, false><<<tgrid, 64, 0, s>>>(md, C);
     k_vox_reduce<M><<<unsigned((C.vox_off[Lm] + kBlock / 64 - 1) / (kBlock / 64)), kBlock, 0, s>>>(C);
     k_corner<M, false><<<cgrid, kBlock, 0, s>>>(C);

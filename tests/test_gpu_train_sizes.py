@@ -54,10 +54,12 @@ KINK_FUSED = (32, 32, False, 16384)
 @pytest.mark.parametrize("m,H,xyz,P", [
     pytest.param(*c, marks=pytest.mark.xfail(reason="a ReLU undetermined in FP32")) if c == KINK_FUSED else c
     for c in [(m, H, xyz, P) for m in (8, 16, 32) for H in (32, 64, 128) for xyz in (True, False)
-              for P in (16384, 16391)]])
+              for P in (16384, 16391)]
+    + [(m, H, xyz, P) for m, H, xyz in ((8, 32, False), (16, 64, True), (32, 128, True))
+       for P in (1023, 1024, 1041, 4097)]])
 def test_fused(m, H, xyz, P):
-    """Every width of the fused large-batch kernel, at whole tiles and at a
-    remainder.  Bars as above, but one ReLU that FP32 does not resolve may move
+    """Every width of the fused decoder kernel, at whole tiles and at a
+    remainder, and around its smallest batch.  Bars as above, but one ReLU that FP32 does not resolve may move
     single feature rows (to 4e-4 of the largest in the batch noted above)."""
     case = make_case(W.tiny_shape(), 16, 3, m, H, sigma=0.1, with_xyz=xyz)
     x, tgt = points(case, np.random.default_rng(P + m), P, 16)
