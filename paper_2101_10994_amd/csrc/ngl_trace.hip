@@ -40,6 +40,21 @@ static int trace_by_width(const ngl_model& m, const TraceArgs& A, hipStream_t s)
   NGL_BY_WIDTH(m.feat_dim, trace_run, m, A, s)
 }
 
+// Evaluations before the rays still running are parked for the lanes-per-ray
+// kernel: NGL_OPT_TRACE_PAUSE1, and less on few rays.  One lane per ray fills
+// the chip from about 2^20 rays on; below, every evaluation takes its latency
+// however few there are, and a group of lanes per ray has the shorter one (6 us
+// against 8).  The first phase ends after one evaluation per 20,480 rays:
+// 96 x 64 rays of the 5-LOD model 652 us a frame against 1038 with 24, 320 x
+// 240 972 against 1277, 512 x 384 1364 against 1588 (and 1479 with 1); at 640 x
+// 480 with a LOD per ray 16 evaluations take 1760, 24 1788 and 8 1874, and at
+// 1024 x 1024 24 take 3704, 16 3772.  The results are the same bit for bit.
+static int first_pause(const ngl_model& m, int64_t R) {
+  const int p = option(NGL_OPT_TRACE_PAUSE1);
+  const bool wide = option(NGL_OPT_TRACE_WIDE) == 1 && (m.w_dtype == NGL_BF16 || option(NGL_OPT_F32_DECODER) == 1);
+  return wide ? int(std::min<int64_t>(p, std::max<int64_t>(1, R / 20480))) : p;
+}
+
 // Workspace of the phased trace: counters ([0..1] parked per phase, [4..6]
 // queue heads), parked state per ray and two ping-pong id lists.
 struct PhaseWS {
@@ -236,7 +251,9 @@ int ngl_sphere_trace(const ngl_model* m, const float* o, const float* d, int64_t
   // are parked and served again from a dense queue, so the long grazing
   // rays finish in full wavefronts instead of a tail of near-empty ones.
   int pause[2], np = 0;
-  const int p1 = option(NGL_OPT_TRACE_PAUSE1), p2 = option(NGL_OPT_TRACE_PAUSE2);
+  const int p2 = option(NGL_OPT_TRACE_PAUSE2);
+  // (a second one-lane phase is asked for: the counts stand)
+  const int p1 = p2 > option(NGL_OPT_TRACE_PAUSE1) ? option(NGL_OPT_TRACE_PAUSE1) : first_pause(*m, R);
   if (p1 > 0 && p1 < params->max_steps) pause[np++] = p1;
   if (p2 > (np ? p1 : 0) && p2 < params->max_steps) pause[np++] = p2;
   if (np == 0) return trace_by_width(*m, A, s);
@@ -323,7 +340,7 @@ int ngl_sphere_trace_lod(const ngl_model* m, const float* o, const float* d, int
   // Phased (matrix-core decoders, workspace large enough, a pause count
   // below max_steps and the wide phase enabled): rays still running at
   // the pause are parked per group and finished eight lanes per ray.
-  const int pause = option(NGL_OPT_TRACE_PAUSE1);
+  const int pause = first_pause(*m, R);
   const bool phased = ws_bytes >= LodWS::bytes_phased(R) && pause > 0 && pause < params->max_steps &&
                       option(NGL_OPT_TRACE_WIDE) == 1 &&
                       (m->w_dtype == NGL_BF16 || option(NGL_OPT_F32_DECODER) == 1);
@@ -533,7 +550,7 @@ int ngl_render_batch(const ngl_model* models, const void* table, const ngl_view*
   B.clock = frame_clock;
   // Phased as ngl_sphere_trace: rays still running at the pause count are
   // parked per view and finished by the lanes-per-ray kernel.
-  const int pause = option(NGL_OPT_TRACE_PAUSE1);
+  const int pause = first_pause(m0, L.R_total);
   if (!(pause > 0 && pause < params->max_steps && option(NGL_OPT_TRACE_WIDE) == 1))
     return batch_by_width(m0, B, any_blend, s);
   B.pause_at = pause;
