@@ -301,13 +301,16 @@ __global__ __launch_bounds__(64 * NW) void k_query_coop(ngl_model md, const floa
       vlast = vn = -1;
     }
     const float a = act ? (alpha_pp ? alpha_pp[p] : alpha) : 0.0f;
+    // 16 points are one tile in any order: a point of 16-bit features takes 8.9 us
+    // instead of 10.0 without the ordering (m = 32, h = 128)
+    PointOrder order{int(threadIdx.x & 63), int(threadIdx.x & 63)};
+    if (P - base > 16) order = order_by_depth(vox, Lp, act);
     float out;
     if constexpr (STREAMED)
       out = tile_eval<M, FT, DEC, true, true>(md, S, x, vox, pack_cell(cx, cy, cz), act, act && blend, a, lod, Lp, b2a,
-                                              b2b, l1s, l1, order_by_depth(vox, Lp, act));
+                                              b2b, l1s, l1, order);
     else
-      out = coop_eval<M, FT, DEC, true>(md, S, x, vox, cx, cy, cz, vn, act, lod, Lp, blend, a, b2a, b2b, l1s, l1,
-                                        order_by_depth(vox, Lp, act));
+      out = coop_eval<M, FT, DEC, true>(md, S, x, vox, cx, cy, cz, vn, act, lod, Lp, blend, a, b2a, b2b, l1s, l1, order);
     if (act) {
       sdf[p] = out;
       if (valid) valid[p] = vlast >= 0 ? 1 : 0;

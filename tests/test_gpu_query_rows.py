@@ -45,3 +45,19 @@ def test_not_a_number():
     assert torch.equal(torch.isinf(rows), torch.isinf(lanes))
     f = torch.isfinite(lanes)
     assert (rows[f] - lanes[f]).abs().max() <= 1e-5
+
+
+@pytest.mark.parametrize("fd,wd", [("f32", "f32"), ("f16", "bf16")])
+def test_few_points_are_the_batch(fd, wd):
+    """Up to 16 points are one tile and keep their order, more are ordered by
+    depth: a point's result is the same bits in any batch."""
+    import torch
+    from paper_2101_10994_amd import ngl
+    case = make_case(W.tiny_shape(), 16, 3, 32, 128, sigma=0.1, feat_dtype=fd, w_dtype=wd)
+    rng = np.random.default_rng(9)
+    pts = np.concatenate([W.points_in_cells(rng, case.ijk, 16, 200), W.uniform_points(rng, 200)])
+    x = torch.from_numpy(W.soa(rng.permutation(pts).astype(np.float32))).cuda()
+    gm = case.gpu_model()
+    full = ngl.query_sdf(gm, x, 3)["sdf"]
+    for n in (1, 15, 16, 17, 64, 272, 273):
+        assert torch.equal(ngl.query_sdf(gm, x[:, :n].contiguous(), 3)["sdf"], full[:n]), n
