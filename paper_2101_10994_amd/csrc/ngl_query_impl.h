@@ -181,7 +181,7 @@ __global__ __launch_bounds__(64 * NW) void k_query_mfma(ngl_model md, const floa
 // coarsest ones), most first, so that points in empty space share tiles
 // that skip the fine levels; lanes without a point come last.  2^20 FP32
 // queries, half of them uniform in the box (they have 2.7 of 5 levels on
-// average): 0.209 -> 0.193 ms; 2^22 blended queries of the 7-LOD 16-bit model
+// average): 0.209 -> 0.187 ms; 2^22 blended queries of the 7-LOD 16-bit model
 // 0.829 -> 0.766 ms.
 __device__ __forceinline__ PointOrder order_by_depth(const int* vox, int Lp, bool act) {
   const int lane = threadIdx.x & 63;
