@@ -1,0 +1,42 @@
+"""Decoder gradients under upstream gradients of mixed sign, where the sums
+over the points cancel: every ReLU is on and every feature zero, so that db1
+and the position columns of dW1 are w2 times plain sums of the upstream
+gradients, formed here in FP64.  A sum of n terms g carries independent
+roundings, of 2^-24 of the partial sums, whose size is that of |g|_2: the bar
+is 2^-22 |g|_2, the result's own rounding beside it.  (Roundings of one sign
+grow with n / |g|_2 instead and miss it from some 2^16 points on.)"""
+import numpy as np
+import pytest
+
+from paper_2101_10994_amd import workloads as W
+
+from cases import make_case
+
+pytestmark = pytest.mark.gpu
+
+
+def backward(case, x, up):
+    import torch
+    from paper_2101_10994_amd import ngl
+    g = ngl.backward_all_lods(case.gpu_model(), torch.from_numpy(x).cuda(), torch.from_numpy(up).cuda())
+    host = lambda ts: [t.cpu().numpy().astype(np.float64) for t in ts]
+    return dict(dfeat=host(g.dfeat), dW1=host(g.dW1), db1=host(g.db1), dw2=host(g.dw2),
+                db2=g.db2.cpu().numpy().astype(np.float64))
+
+
+@pytest.mark.parametrize("m,H", [(8, 32), (16, 64), (32, 32), (32, 64), (32, 128)])
+@pytest.mark.parametrize("P", [1024, 65537, 262144, 300_001])
+def test_sums_that_cancel(P, m, H):
+    case = make_case(W.tiny_shape(), 16, 3, m, H, sigma=0.0)
+    case.b1 = [np.full_like(b, 64.0) for b in case.b1]
+    assert all(np.abs(w[:, :3]).sum(1).max() < 64.0 for w in case.W1)
+    rng = np.random.default_rng(P + m + H)
+    x = W.soa(rng.uniform(-1, 1, (P, 3)).astype(np.float32))
+    up = (rng.normal(size=(case.L, P)) / P).astype(np.float32)
+    got = backward(case, x, up)
+    for l in range(case.L):
+        g, w2 = up[l].astype(np.float64), np.asarray(case.w2[l])[:, None]
+        terms = np.concatenate([g[None], g * x.astype(np.float64)])  # of db1 and three columns of dW1
+        ref, size = w2 * terms.sum(1), np.abs(w2) * np.sqrt((terms ** 2).sum(1))
+        err = np.abs(np.concatenate([got["db1"][l][:, None], got["dW1"][l][:, :3]], 1) - ref)
+        assert (err <= 2.0 ** -22 * size + 2.0 ** -23 * np.abs(ref)).all(), (l, (err / size).max())
