@@ -556,20 +556,23 @@ __global__ __launch_bounds__(kBlock) void k_point_sums(ngl_model md, PointArgs A
 // k_dec_grad; 2^19 points take 984 us a step instead of 974.  The masks are kept as bits: of
 // point j's units for the adjoint, and through LDS of a unit's points for G;
 // their BF16 value is 2, which is one bit, against g / 2.
-// As a = W1 [x, z] + b1, dw2 = W1 G + b1 G_1; dW1 = w2 G and db1 = w2 G_1 are
-// left to k_dec_reduce.
+// dW1 = w2 G and db1 = w2 G_1 are left to k_dec_reduce.  dw2 is the plain sum
+// of g relu(a), per lane in LDS (32 more registers are not there): as W1 G + b1
+// G_1 it would lose what cancels between the two, and take a point's NaN to every
+// unit (2^19 points 1023 us a step against 984 that way).
 // A wavefront runs its range of tiles for LOD after LOD from the finest down
 // and adds dpsi_{l+1}, which the same lane wrote, to dz_l.  The block shares
 // the decoder's fragments in LDS; each wavefront keeps its sums in registers,
 // which the block adds up in a fixed order after each LOD.
-// Bound by the matrix instructions (2304 cycles per tile and LOD forward, 960
+// Bound by the matrix instructions (2304 cycles per tile and LOD forward, 1088
 // for the rest at M = 32, H = 128) and about as much vector work beside the
 // FP32 ones, which does not overlap with them.  2^19 points, 5 LODs, M = 32,
 // H = 128: 569 us (764 with FP32 matrix instructions throughout), and 141 for
 // the sums before it, against 1040 us for one lane per point (k_point) and 853
-// for the gradients (k_dec_grad).  Errors against FP64, median over four widths
-// and eight sizes: feature gradients 6.2e-8 (6.3e-8 before), dW1 4.6e-8 (5.1e-8),
-// dw2 3.7e-8 (4.2e-8).
+// for the gradients (k_dec_grad).  Errors against FP64, median over four
+// widths, six sizes and six seeds, here and of those kernels: feature gradients
+// 6.4e-8 (6.5e-8), dW1 3.6e-8 (5.2e-8), dw2 2.9e-8 (4.4e-8) in training steps; 1.4e-7
+// (1.7e-7), 7.0e-8 (1.8e-7), 1.7e-7 (2.6e-7) with upstream gradients of mixed sign.
 template <int M, bool XYZ, int HT>
 struct Fused {
   static constexpr int OFF = XYZ ? 3 : 0;
@@ -586,6 +589,7 @@ struct Fused {
   static constexpr int W = DIN + 2;            // a row of the partial sums: dW1, db1, dw2
   static constexpr int NW = kFusedWaves;
   static constexpr int WS = 160;               // scratch of a wavefront: masks [2][4][16], g [2][16]
+  static constexpr int DS = HT * 256;          // and its lanes' sums of dw2: [HT][64][4]
   // LDS, in floats
   static constexpr int FW4 = 0;
   static constexpr int FW1 = FW4 + HT * K4 * 256;
@@ -595,7 +599,7 @@ struct Fused {
   static constexpr int TRB = W2 + H;           // the scratch, and the sums after a LOD
   static constexpr int ACC = HT * CT * 4;      // accumulators of G per lane
   static constexpr int SUM = (ACC + 1) * 64;   // one wavefront's sums
-  static constexpr int FLOATS = TRB + std::max({NW * WS, NW / 2 * SUM, H * W});
+  static constexpr int FLOATS = TRB + std::max({NW * (WS + DS), NW / 2 * SUM, H * W});
 };
 
 struct FusedArgs {
@@ -633,6 +637,7 @@ __global__ __launch_bounds__(64 * kFusedWaves) void k_dec_fused(ngl_model md, Fu
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // so tiles are uniform: scalar bases
   uint32_t* mw = reinterpret_cast<uint32_t*>(sm + S::TRB + w * S::WS);
   float* gw = sm + S::TRB + w * S::WS + 128;
+  float4* dw2 = reinterpret_cast<float4*>(sm + S::TRB + NW * S::WS + w * S::DS);
   const int64_t T = (P + 15) / 16, slots = int64_t(gridDim.x) * NW, me = int64_t(blockIdx.x) * NW + w;
   const int t0 = int(T * me / slots), t1 = int(T * (me + 1) / slots);
   // The three position arrays lie in one workspace.  Distances, so that a
@@ -696,6 +701,8 @@ __global__ __launch_bounds__(64 * kFusedWaves) void k_dec_fused(ngl_model md, Fu
 #pragma unroll
       for (int n = 0; n < CT; ++n) acc[h][n] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
     int g = lane >> 4, j = lane & 15;
+#pragma unroll
+    for (int h = 0; h < HT; ++h) dw2[64 * h + lane] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     // A tile's inputs 4s + g of point j and its target are requested while the
     // tile before is in its backward pass (b is free then).
     float b[2][S::KS], up[2] = {0.0f, 0.0f};
@@ -820,6 +827,17 @@ __global__ __launch_bounds__(64 * kFusedWaves) void k_dec_fused(ngl_model md, Fu
         }
         gr = live ? gr : 0.0f;
         ab2 += gr;
+        if (live) {
+#pragma unroll
+          for (int h = 0; h < HT; ++h) {
+            float4 d = dw2[64 * h + ln];
+            d.x = fmaf(gr, fmaxf(a[h][0], 0.0f), d.x);
+            d.y = fmaf(gr, fmaxf(a[h][1], 0.0f), d.y);
+            d.z = fmaf(gr, fmaxf(a[h][2], 0.0f), d.z);
+            d.w = fmaf(gr, fmaxf(a[h][3], 0.0f), d.w);
+            dw2[64 * h + ln] = d;
+          }
+        }
         if (A.sdf_all && live && g == 0) (A.sdf_all + int64_t(L - 1) * P)[id[q]] = out;
         gr *= 0.5f;  // the masks' BF16 value is 2
         mw[64 * q + ln] = on;
@@ -944,6 +962,18 @@ __global__ __launch_bounds__(64 * kFusedWaves) void k_dec_fused(ngl_model md, Fu
     g = ln >> 4, j = ln & 15;
 #pragma unroll
     for (int off = 8; off >= 1; off >>= 1) ab2 += __shfl_xor(ab2, off, 64);
+    // dw2 over the lanes' points, into a free column of G's last tile
+#pragma unroll
+    for (int h = 0; h < HT; ++h) {
+      const float4 d = dw2[64 * h + ln];
+      double v[4] = {d.x, d.y, d.z, d.w};
+#pragma unroll
+      for (int off = 8; off >= 1; off >>= 1)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[r] += __shfl_xor(v[r], off, 64);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc[h][CT - 1][r] = j - S::X0 == 4 ? float(v[r]) : acc[h][CT - 1][r];
+    }
     float* sums = sm + S::TRB;
 #pragma unroll 1
     for (int half = NW / 2; half >= 1; half >>= 1) {
@@ -982,7 +1012,7 @@ __global__ __launch_bounds__(64 * kFusedWaves) void k_dec_fused(ngl_model md, Fu
         for (int n = 0; n < CT; ++n) {
           // the entry's column, or none
           const int c = j - S::X0;
-          const int col = n < CT - 1 || c < 0 ? OFF + NT * j + n : c < OFF ? c : c == 3 ? DIN : -1;
+          const int col = n < CT - 1 || c < 0 ? OFF + NT * j + n : c < OFF ? c : c == 3 ? DIN : c == 4 ? DIN + 1 : -1;
           if (col >= 0) {
 #pragma unroll
             for (int r = 0; r < 4; ++r) row[(4 * g + r) * S::W + col] = acc[h][n][r];
@@ -990,21 +1020,6 @@ __global__ __launch_bounds__(64 * kFusedWaves) void k_dec_fused(ngl_model md, Fu
         }
       }
       if (lane == 0) F.part_b2[int64_t(L - 1) * kFusedGrid + blockIdx.x] = ab2;
-    }
-    __syncthreads();
-    // dw2 = W1 G_[x,z] + b1 G_1, from the forward pass's fragments
-    for (int k = threadIdx.x; k < S::H; k += 64 * NW) {
-      const int hk = k >> 4, uk = k & 15;
-      float* row = sums + k * S::W;
-      double d = double(sm[S::B1 + k]) * row[DIN];  // may cancel
-#pragma unroll
-      for (int i = 0; i < DIN; ++i) {
-        const int at = uk + 16 * (i % 4);
-        const float wk = i < 16 * S::K4 ? sm[S::FW4 + ((hk * S::K4 + i / 16) * 64 + at) * 4 + i / 4 % 4]
-                                        : sm[S::FW1 + (hk * S::K1 + (i - 16 * S::K4) / 4) * 64 + at];
-        d = fma(double(wk), double(row[i]), d);
-      }
-      row[DIN + 1] = float(d);
     }
     __syncthreads();
     float* dst = F.part + ((L - 1) * F.slots + blockIdx.x) * (S::H * S::W);
@@ -1134,7 +1149,7 @@ struct DecOut {
   float* dW1[NGL_MAX_LODS];
   float* db1[NGL_MAX_LODS];
   float* dw2[NGL_MAX_LODS];
-  const float* w2[NGL_MAX_LODS];  // factor of dW1 and db1, or null
+  const float* w2[NGL_MAX_LODS];  // FUSED: factor of dW1 and db1
   float* db2;
   float* loss;             // nullable: the sum of loss_part[0, nloss) times inv_p
   const float* loss_part;
@@ -1145,9 +1160,12 @@ struct DecOut {
 // 64 entries of a LOD's sums per block, lane = entry, so that the partials are
 // read in whole lines: each wavefront adds the slots w, w + 4, ... in order and
 // the four are added in order (a fixed order, so the result is reproducible).
+// FUSED: the partials of k_dec_fused, whose dW1 and db1 lack the factor w2, are
+// added in FP64, k_dec_grad's in FP32.
 // The block after the entries adds db2 and, at LOD 1, the loss.  256 slots of 5
 // LODs of the 128-unit decoder (24 MB) take under 10 us; a wavefront per entry,
 // its lanes a stride of 19 KB apart, took 49.
+template <bool FUSED>
 __global__ __launch_bounds__(kBlock) void k_dec_reduce(const float* __restrict__ part, int64_t stride, int nslots,
                                                        const float* __restrict__ part_b2, int nb2, int H, int din,
                                                        DecOut O) {
@@ -1164,13 +1182,14 @@ __global__ __launch_bounds__(kBlock) void k_dec_reduce(const float* __restrict__
     if (L == 1 && O.loss) loss_reduce(O.loss_part, O.nloss, O.inv_p, O.loss);
     return;
   }
-  __shared__ float sum[kBlock / 64][64];
+  typedef std::conditional_t<FUSED, double, float> Sum;
+  __shared__ Sum sum[kBlock / 64][64];
   const int W = din + 2;
   const int e = blockIdx.x * 64 + lane;  // entry of [H][din+2]
-  float s = 0.0f;
+  Sum s = 0;
   if (e < H * W) {  // eight sums of every 32nd slot, then pairwise: short chains
     const float* src = part + (L - 1) * stride * (H * W) + e;
-    float q[8] = {};
+    Sum q[8] = {};
     int j = w;
     for (; j + 28 < nslots; j += 32)
 #pragma unroll
@@ -1183,11 +1202,11 @@ __global__ __launch_bounds__(kBlock) void k_dec_reduce(const float* __restrict__
   if (w == 0 && e < H * W) {
     double t = ((double(sum[0][lane]) + sum[1][lane]) + sum[2][lane]) + sum[3][lane];
     const int k = e / W, i = e % W;
-    if (O.w2[L - 1] && i <= din) t *= O.w2[L - 1][k];
-    s = float(t);
-    if (i < din) O.dW1[L - 1][k * din + i] = s;
-    else if (i == din) O.db1[L - 1][k] = s;
-    else O.dw2[L - 1][k] = s;
+    if (FUSED && i <= din) t *= O.w2[L - 1][k];
+    const float v = float(t);
+    if (i < din) O.dW1[L - 1][k * din + i] = v;
+    else if (i == din) O.db1[L - 1][k] = v;
+    else O.dw2[L - 1][k] = v;
   }
 }
 
@@ -1653,7 +1672,7 @@ static int run_train(const ngl_model& md, const float* x, const float* target, c
     O.dW1[l] = dW1[l];
     O.db1[l] = db1[l];
     O.dw2[l] = dw2[l];
-    O.w2[l] = fused ? static_cast<const float*>(md.w2[l]) : nullptr;
+    O.w2[l] = static_cast<const float*>(md.w2[l]);
   }
   O.db2 = db2;
   O.loss = target ? loss : nullptr;
@@ -1662,7 +1681,7 @@ static int run_train(const ngl_model& md, const float* x, const float* target, c
   O.inv_p = 1.0f / float(P);
   const int din = M + (XYZ ? 3 : 0);
   const int H = md.hidden;
-  k_dec_reduce<<<dim3(unsigned((H * (din + 2) + 63) / 64) + 1, Lm), kBlock, 0, s>>>(
+  (fused ? k_dec_reduce<true> : k_dec_reduce<false>)<<<dim3(unsigned((H * (din + 2) + 63) / 64) + 1, Lm), kBlock, 0, s>>>(
       w.dec_part, int64_t(kDecGrid) * PH, nslots, w.dec_b2, nb2, H, din, O);
   // 4. feature gradients
   FeatArgs C{};

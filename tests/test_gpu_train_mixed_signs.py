@@ -40,3 +40,28 @@ def test_sums_that_cancel(P, m, H):
         ref, size = w2 * terms.sum(1), np.abs(w2) * np.sqrt((terms ** 2).sum(1))
         err = np.abs(np.concatenate([got["db1"][l][:, None], got["dW1"][l][:, :3]], 1) - ref)
         assert (err <= 2.0 ** -22 * size + 2.0 ** -23 * np.abs(ref)).all(), (l, (err / size).max())
+
+
+@pytest.mark.parametrize("m,H", [(8, 32), (16, 64), (32, 128)])
+@pytest.mark.parametrize("P", [1024, 65537])
+def test_steep_decoder(P, m, H):
+    """dw2 of units 32 (x - x_k), x around x_k: the sum of g relu(a), which is
+    small beside W1's and b1's shares of it.  Positions and offsets are
+    multiples of 2^-9 and 2^-4, so that every pre-activation is exact; the bar
+    is that of a plain sum of its terms."""
+    case = make_case(W.tiny_shape(), 16, 3, m, H, sigma=0.0)
+    rng = np.random.default_rng(P + m + H)
+    xk = (0.5 + 2.0 ** -9 * np.arange(H))
+    for l in range(case.L):
+        case.W1[l] = np.zeros_like(case.W1[l])
+        case.W1[l][:, 0] = 32.0
+        case.b1[l] = -32.0 * xk
+    x = np.concatenate([0.5 + 2.0 ** -9 * rng.integers(0, H, (1, P)), rng.uniform(-1, 1, (2, P))]).astype(np.float32)
+    up = (rng.normal(size=(case.L, P)) / P).astype(np.float32)
+    got = backward(case, x, up)
+    a = np.maximum(32.0 * (x[0].astype(np.float64)[None] - xk[:, None]), 0.0)
+    for l in range(case.L):
+        terms = up[l].astype(np.float64)[None] * a
+        ref, size = terms.sum(1), np.sqrt((terms ** 2).sum(1))
+        err = np.abs(got["dw2"][l] - ref)
+        assert (err <= 2.0 ** -22 * size + 2.0 ** -23 * np.abs(ref)).all(), (l, (err / size.clip(1e-30)).max())

@@ -1,0 +1,64 @@
+"""A point that is not finite spoils the same gradient entries in batches of
+every size: batches of the fused decoder kernel (from 1,024 points on, whole
+tiles and remainders, and one LOD per block or all in turn) have non-finite
+entries exactly where the smallest batch with that point has them."""
+import numpy as np
+import pytest
+
+from paper_2101_10994_amd import workloads as W
+
+from cases import make_case
+from test_gpu_train_mixed_signs import backward
+
+pytestmark = pytest.mark.gpu
+
+
+def finite_entries(case, x, up):
+    g = backward(case, x, up)
+    return [np.isfinite(t) for n in ("dfeat", "dW1", "db1", "dw2") for t in g[n]] + [np.isfinite(g["db2"])]
+
+
+def batch(case, P, where, change):
+    """P points, the one at `where` (of the order given) changed."""
+    rng = np.random.default_rng(7)
+    x = W.soa(np.concatenate([W.points_in_cells(rng, case.ijk, 16, P // 2), W.uniform_points(rng, P - P // 2)])
+              .astype(np.float32))
+    up = (rng.normal(size=(case.L, P)) / P).astype(np.float32)
+    x[:, where] = 0.3, -0.2, 0.6
+    change(x, up, where)
+    return x, up
+
+
+def nan_coordinate(x, up, i):
+    x[1, i] = np.nan
+
+
+def inf_coordinate(x, up, i):
+    x[0, i] = np.inf
+
+
+@pytest.mark.parametrize("m,H,xyz", [(8, 32, True), (16, 64, False), (32, 128, True)])
+@pytest.mark.parametrize("change", [nan_coordinate, inf_coordinate], ids=lambda f: f.__name__)
+def test_point(change, m, H, xyz):
+    case = make_case(W.tiny_shape(), 16, 3, m, H, sigma=0.1, with_xyz=xyz)
+    ref = finite_entries(case, *batch(case, 900, 5, change))
+    for P, where in ((1024, 5), (1041, 1040), (16384, 77), (65537, 65536), (262151, 9)):
+        got = finite_entries(case, *batch(case, P, where, change))
+        assert all(np.array_equal(a, b) for a, b in zip(got, ref)), P
+
+
+@pytest.mark.parametrize("m,H", [(8, 32), (32, 128)])
+@pytest.mark.parametrize("P", [900, 1024, 16384])
+def test_feature(P, m, H):
+    """A NaN in a feature table turns the units of its points off: it reaches
+    its own column of dW1 and nothing else."""
+    case = make_case(W.tiny_shape(), 16, 3, m, H, sigma=0.1)
+    case.feats[2][case.otree.export_corners(3)[0][0], 1] = np.nan
+    centre = -1.0 + (case.otree.export_depth(4)["ijk"][0] + 0.5) * (2.0 / 16)
+
+    def inside(x, up, i):
+        x[:, i] = centre
+    g = backward(case, *batch(case, P, 5, inside))
+    assert np.isnan(g["dW1"][2][:, 3 + 1]).all()
+    g["dW1"][2][:, 3 + 1] = 0.0
+    assert all(np.isfinite(t).all() for n in ("dfeat", "dW1", "db1", "dw2") for t in g[n])
