@@ -863,13 +863,18 @@ __global__ __launch_bounds__(64 * kFusedWaves) void k_dec_fused(ngl_model md, Fu
               d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf, m, d, 0, 0, 0);
             }
         }
+        // a point without a unit that is on passes nothing back, also where its
+        // upstream gradient is not finite
+        uint32_t some = uint32_t(__ballot(on != 0u)) | uint32_t(__ballot(on != 0u) >> 32);
+        some = (some | some >> 16) >> j & 1u;
         if (live && 4 * g < S::MT) {
+          const float gz = some ? gr : 0.0f;
           float4* d4 = reinterpret_cast<float4*>(dl + p0 * M + j * M + zoff);
           float v[4 * NT];
 #pragma unroll
           for (int r = 0; r < 4; ++r)
 #pragma unroll
-            for (int n = 0; n < NT; ++n) v[NT * r + n] = fmaf(gr, d1[n][r], gr * d2[n][r]) + (above ? u[NT * r + n] : 0.0f);
+            for (int n = 0; n < NT; ++n) v[NT * r + n] = fmaf(gz, d1[n][r], gz * d2[n][r]) + (above ? u[NT * r + n] : 0.0f);
 #pragma unroll
           for (int e = 0; e < NT; ++e) d4[e] = make_float4(v[4 * e], v[4 * e + 1], v[4 * e + 2], v[4 * e + 3]);
         }
@@ -896,6 +901,7 @@ __global__ __launch_bounds__(64 * kFusedWaves) void k_dec_fused(ngl_model md, Fu
       }
       wave_sync_lds();
       uint4 y[CT][3];  // g times them, in three BF16 parts
+      float spoilt = 0.0f;  // NaN where one is not finite
 #pragma unroll
       for (int q = 0; q < 2; ++q) {
         const float4 gv = *reinterpret_cast<const float4*>(gw + 16 * q + 4 * g);
@@ -918,6 +924,7 @@ __global__ __launch_bounds__(64 * kFusedWaves) void k_dec_fused(ngl_model md, Fu
             for (int k = 0; k < 3; ++k) {
               const uint32_t t2 = pack_bf16(v0, v1);
               const float part0 = __uint_as_float(t2 << 16), part1 = __uint_as_float(t2 & 0xffff0000u);
+              if (k == 0) spoilt = fmaf(part1, 0.0f, fmaf(part0, 0.0f, spoilt));
               v0 = k == 0 ? fmaf(z0, gp[e], -part0) : v0 - part0;  // of the exact products
               v1 = k == 0 ? fmaf(z1, gp[e + 1], -part1) : v1 - part1;
               if (q == 0 && e == 0) y[n][k].x = t2;
@@ -927,6 +934,36 @@ __global__ __launch_bounds__(64 * kFusedWaves) void k_dec_fused(ngl_model md, Fu
             }
           }
         }
+      }
+      // Products that are not finite would reach the units that are off, a mask
+      // being a factor: these points are added one by one.
+      if (__builtin_expect(__any(spoilt != 0.0f), 0)) {
+#pragma unroll 1
+        for (int i = 0; i < 32; ++i) {
+          const int64_t p = 16 * int64_t(t) + i;
+          if (p >= 16 * int64_t(t1) || p >= P) break;
+          const uint32_t on = mw[64 * (i >> 4) + 16 * g + (i & 15)];
+          const float gi = 2.0f * gw[i];
+          float v[CT];
+#pragma unroll
+          for (int n = 0; n < CT; ++n) {
+            const int c = j - S::X0;
+            if (n < CT - 1 || c < 0) v[n] = zl[p * M + NT * j + n];
+            else v[n] = c == 3 ? 1.0f : c < OFF ? (X0 + p)[(c == 1 ? dx1 : 0) + (c == 2 ? dx2 : 0)] : 0.0f;
+          }
+#pragma unroll
+          for (int h = 0; h < HT; ++h)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              const float ga = on >> (2 * h + r / 2 + 16 * (r % 2)) & 1u ? gi : 0.0f;
+#pragma unroll
+              for (int n = 0; n < CT; ++n) acc[h][n][r] = fmaf(ga, v[n], acc[h][n][r]);
+            }
+        }
+#pragma unroll
+        for (int n = 0; n < CT; ++n)
+#pragma unroll
+          for (int k = 0; k < 3; ++k) y[n][k] = make_uint4(0u, 0u, 0u, 0u);
       }
       // unit 16h + j of the points 4g + e: bit 2h of the low half after the shift
       uint32_t mp[4];

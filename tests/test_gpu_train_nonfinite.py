@@ -24,7 +24,7 @@ def batch(case, P, where, change):
     x = W.soa(np.concatenate([W.points_in_cells(rng, case.ijk, 16, P // 2), W.uniform_points(rng, P - P // 2)])
               .astype(np.float32))
     up = (rng.normal(size=(case.L, P)) / P).astype(np.float32)
-    x[:, where] = 0.3, -0.2, 0.6
+    x[:, where] = -1.0 + (case.ijk[7] + 0.4) * (2.0 / 16)
     change(x, up, where)
     return x, up
 
@@ -37,14 +37,33 @@ def inf_coordinate(x, up, i):
     x[0, i] = np.inf
 
 
+def nan_upstream(x, up, i):
+    up[1, i] = np.nan
+
+
+def inf_upstream(x, up, i):
+    up[:, i] = -np.inf
+
+
 @pytest.mark.parametrize("m,H,xyz", [(8, 32, True), (16, 64, False), (32, 128, True)])
-@pytest.mark.parametrize("change", [nan_coordinate, inf_coordinate], ids=lambda f: f.__name__)
+@pytest.mark.parametrize("change", [nan_coordinate, inf_coordinate, nan_upstream, inf_upstream], ids=lambda f: f.__name__)
 def test_point(change, m, H, xyz):
     case = make_case(W.tiny_shape(), 16, 3, m, H, sigma=0.1, with_xyz=xyz)
     ref = finite_entries(case, *batch(case, 900, 5, change))
     for P, where in ((1024, 5), (1041, 1040), (16384, 77), (65537, 65536), (262151, 9)):
         got = finite_entries(case, *batch(case, P, where, change))
         assert all(np.array_equal(a, b) for a, b in zip(got, ref)), P
+
+
+@pytest.mark.parametrize("m,H", [(8, 32), (32, 128)])
+def test_every_unit_off(m, H):
+    """Nothing passes back to features and first layers through units that are off."""
+    case = make_case(W.tiny_shape(), 16, 3, m, H, sigma=0.1)
+    case.b1 = [np.full_like(b, -64.0) for b in case.b1]
+    for P in (1024, 16391):
+        g = backward(case, *batch(case, P, 5, nan_upstream))
+        assert all((t == 0.0).all() for n in ("dfeat", "dW1", "db1") for t in g[n]), P
+        assert np.isnan(g["dw2"][1]).all() and np.isnan(g["db2"][1])
 
 
 @pytest.mark.parametrize("m,H", [(8, 32), (32, 128)])
