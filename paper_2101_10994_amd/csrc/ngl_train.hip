@@ -52,6 +52,7 @@ constexpr int64_t kPointWaveMax = 16384;
 // k_point_wave and 68 with it, of 1,024 78 and 74, of 4,096 176 and 119, of
 // 16,383 403 and 161; at M = 8, H = 32 the two meet there as well.
 constexpr int64_t kFusedMin = 1024;
+inline bool fused_widths(int M, int H) { return M <= 32 && (H == 32 || H == 64 || H == 128); }
 // Up to this many points k_dec_fused gives each LOD a row of blocks instead of
 // having every block do all LODs in turn: a block's decoder is loaded and its
 // sums are added up once instead of for every LOD (14 us each time, against
@@ -1576,8 +1577,11 @@ static TrainWS carve(const ngl_model& m, int64_t P, void* base) {
   w.drows = reinterpret_cast<float*>(take(4 * size_t(L) * size_t(P) * size_t(M)));
   w.gs = reinterpret_cast<float*>(take(4 * size_t(L) * size_t(P)));
   w.vox_s = reinterpret_cast<int32_t*>(take(4 * size_t(L) * size_t(P)));
+  // one per point and LOD of k_point_wave, per block of k_point or of k_dec_fused;
+  // for the smaller batches too, so that a workspace serves them all
+  const int64_t wave = std::min<int64_t>(P, (fused_widths(M, H) ? kFusedMin : kPointWaveMax) - 1);
   w.loss_part = reinterpret_cast<float*>(
-      take(4 * size_t(P < kPointWaveMax ? L * P + 1 : std::max<int64_t>((P + kBlock - 1) / kBlock + 1, kFusedGrid))));
+      take(4 * size_t(std::max({L * wave, (P + kBlock - 1) / kBlock, int64_t(kFusedGrid)}))));
   w.dec_part = reinterpret_cast<float*>(take(4 * size_t(L) * kDecGrid * PH * size_t(H) * size_t(din + 2)));
   w.dec_b2 = reinterpret_cast<float*>(take(4 * size_t(L) * kFusedGrid));
   w.cnt_stride = (w.ntiles + 4) / 4 * 4;  // whole 16-byte vectors
@@ -1667,7 +1671,7 @@ static int run_train(const ngl_model& md, const float* x, const float* target, c
   int nslots = 0, nb2 = 0;
   // one fused kernel on the matrix cores where a wavefront's registers hold a
   // decoder's gradients
-  const bool fused = P >= kFusedMin && M <= 32 && (md.hidden == 32 || md.hidden == 64 || md.hidden == 128);
+  const bool fused = P >= kFusedMin && fused_widths(M, md.hidden);
   if (!fused && P < kPointWaveMax) {
     // small batches: one wavefront per point and LOD
     const dim3 wgrid(unsigned((P + kBlock / 64 - 1) / (kBlock / 64)), unsigned(Lm));
