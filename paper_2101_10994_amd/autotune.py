@@ -7,8 +7,9 @@ persistent tracers are launched, never what they compute:
                                  occupancy limit, or a smaller cap);
   * NGL_OPT_TRACE_PAUSE1         evaluation count at which the phased tracer
                                  parks the rays still running and finishes
-                                 them with a group of lanes per ray (24, 12,
-                                 48; 0 = one phase);
+                                 them with a group of lanes per ray (24, the
+                                 default: fewer on few rays; 12, 48; 0 = one
+                                 phase);
   * NGL_OPT_F32_DECODER          FP32 decoder on the vector ALUs or the matrix
                                  cores (FP32 models only).
 Each candidate is timed with HIP events on the current stream (median of a

@@ -11,7 +11,7 @@ namespace ngl {
 static thread_local std::string g_last_error;
 
 // Library options; defaults are the fastest measured choices.
-static std::atomic<int> g_options[NGL_OPT_COUNT] = {{1}, {0}, {0}, {24}, {0}, {1}, {1}, {0}};
+static std::atomic<int> g_options[NGL_OPT_COUNT] = {{1}, {0}, {0}, {kTracePause1}, {0}, {1}, {1}, {0}};
 
 int option(int key) { return (key >= 0 && key < NGL_OPT_COUNT) ? g_options[key].load() : 0; }
 

@@ -40,6 +40,9 @@ void set_error(const char* fmt, ...);
       NGL_FAIL(NGL_E_HIP, "kernel launch failed: %s", hipGetErrorString(e_));  \
   } while (0)
 
+// Default of NGL_OPT_TRACE_PAUSE1.
+constexpr int kTracePause1 = 24;
+
 // Current value of a library option (ngl_set_option).
 int option(int key);
 

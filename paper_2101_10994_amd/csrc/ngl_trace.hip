@@ -41,7 +41,7 @@ static int trace_by_width(const ngl_model& m, const TraceArgs& A, hipStream_t s)
 }
 
 // Evaluations before the rays still running are parked for the lanes-per-ray
-// kernel: NGL_OPT_TRACE_PAUSE1, and less on few rays.  One lane per ray fills
+// kernel: NGL_OPT_TRACE_PAUSE1, and at its default less on few rays.  One lane per ray fills
 // the chip from about 2^20 rays on; below, every evaluation takes its latency
 // however few there are, and a group of lanes per ray has the shorter one (6 us
 // against 8).  The first phase ends after one evaluation per 20,480 rays:
@@ -52,7 +52,8 @@ static int trace_by_width(const ngl_model& m, const TraceArgs& A, hipStream_t s)
 static int first_pause(const ngl_model& m, int64_t R) {
   const int p = option(NGL_OPT_TRACE_PAUSE1);
   const bool wide = option(NGL_OPT_TRACE_WIDE) == 1 && (m.w_dtype == NGL_BF16 || option(NGL_OPT_F32_DECODER) == 1);
-  return wide ? int(std::min<int64_t>(p, std::max<int64_t>(1, R / 20480))) : p;
+  if (p != kTracePause1 || !wide) return p;
+  return int(std::min<int64_t>(p, std::max<int64_t>(1, R / 20480)));
 }
 
 // Workspace of the phased trace: counters ([0..1] parked per phase, [4..6]
@@ -251,11 +252,12 @@ int ngl_sphere_trace(const ngl_model* m, const float* o, const float* d, int64_t
   // are parked and served again from a dense queue, so the long grazing
   // rays finish in full wavefronts instead of a tail of near-empty ones.
   int pause[2], np = 0;
+  int p1 = option(NGL_OPT_TRACE_PAUSE1);
   const int p2 = option(NGL_OPT_TRACE_PAUSE2);
-  // (a second one-lane phase is asked for: the counts stand)
-  const int p1 = p2 > option(NGL_OPT_TRACE_PAUSE1) ? option(NGL_OPT_TRACE_PAUSE1) : first_pause(*m, R);
+  const bool second = p2 > (p1 < params->max_steps ? p1 : 0) && p2 < params->max_steps;
+  if (!second) p1 = first_pause(*m, R);  // else the counts stand
   if (p1 > 0 && p1 < params->max_steps) pause[np++] = p1;
-  if (p2 > (np ? p1 : 0) && p2 < params->max_steps) pause[np++] = p2;
+  if (second) pause[np++] = p2;
   if (np == 0) return trace_by_width(*m, A, s);
   const int phases = np + 1;
   PhaseWS W(ws, R);
