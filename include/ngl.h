@@ -87,9 +87,9 @@ int ngl_version(void);
  *    a phased ngl_sphere_trace parks the rays still running (0..4096, 0 =
  *    no such phase; a second count not above the first is ignored).  The
  *    first is 24 by default, which stands for the measured choice: with a
- *    lanes-per-ray phase and no second count, fewer than 24 * 20480 rays
- *    are parked after R / 20480 evaluations (at least one).  Any other
- *    count is taken as it is.
+ *    lanes-per-ray phase and no second count, fewer than 24 * 20480 rays of
+ *    more than 24 steps are parked after R / 20480 evaluations (at least
+ *    one).  Any other count is taken as it is.
  *  NGL_OPT_TRACE_WIDE: 1 (default) = the last phase of a phased trace
  *    serves each ray with a group of lanes (matrix-core decoders only),
  *    0 = one lane per ray throughout.

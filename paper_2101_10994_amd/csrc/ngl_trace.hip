@@ -49,10 +49,13 @@ static int trace_by_width(const ngl_model& m, const TraceArgs& A, hipStream_t s)
 // 240 972 against 1277, 512 x 384 1364 against 1588 (and 1479 with 1); at 640 x
 // 480 with a LOD per ray 16 evaluations take 1760, 24 1788 and 8 1874, and at
 // 1024 x 1024 24 take 3704, 16 3772.  The results are the same bit for bit.
-static int first_pause(const ngl_model& m, int64_t R) {
+// Traces of at most the default's evaluations stay one launch: what the second
+// would shorten is less than it costs (4 evaluations of 320 x 240 rays of a small
+// model 66 us against 155, 8 with a LOD per ray 149 against 280).
+static int first_pause(const ngl_model& m, int64_t R, int max_steps) {
   const int p = option(NGL_OPT_TRACE_PAUSE1);
   const bool wide = option(NGL_OPT_TRACE_WIDE) == 1 && (m.w_dtype == NGL_BF16 || option(NGL_OPT_F32_DECODER) == 1);
-  if (p != kTracePause1 || !wide) return p;
+  if (p != kTracePause1 || max_steps <= p || !wide) return p;
   return int(std::min<int64_t>(p, std::max<int64_t>(1, R / 20480)));
 }
 
@@ -255,7 +258,7 @@ int ngl_sphere_trace(const ngl_model* m, const float* o, const float* d, int64_t
   int p1 = option(NGL_OPT_TRACE_PAUSE1);
   const int p2 = option(NGL_OPT_TRACE_PAUSE2);
   const bool second = p2 > (p1 < params->max_steps ? p1 : 0) && p2 < params->max_steps;
-  if (!second) p1 = first_pause(*m, R);  // else the counts stand
+  if (!second) p1 = first_pause(*m, R, params->max_steps);  // else the counts stand
   if (p1 > 0 && p1 < params->max_steps) pause[np++] = p1;
   if (second) pause[np++] = p2;
   if (np == 0) return trace_by_width(*m, A, s);
@@ -342,7 +345,7 @@ int ngl_sphere_trace_lod(const ngl_model* m, const float* o, const float* d, int
   // Phased (matrix-core decoders, workspace large enough, a pause count
   // below max_steps and the wide phase enabled): rays still running at
   // the pause are parked per group and finished eight lanes per ray.
-  const int pause = first_pause(*m, R);
+  const int pause = first_pause(*m, R, params->max_steps);
   const bool phased = ws_bytes >= LodWS::bytes_phased(R) && pause > 0 && pause < params->max_steps &&
                       option(NGL_OPT_TRACE_WIDE) == 1 &&
                       (m->w_dtype == NGL_BF16 || option(NGL_OPT_F32_DECODER) == 1);
@@ -552,7 +555,7 @@ int ngl_render_batch(const ngl_model* models, const void* table, const ngl_view*
   B.clock = frame_clock;
   // Phased as ngl_sphere_trace: rays still running at the pause count are
   // parked per view and finished by the lanes-per-ray kernel.
-  const int pause = first_pause(m0, L.R_total);
+  const int pause = first_pause(m0, L.R_total, params->max_steps);
   if (!(pause > 0 && pause < params->max_steps && option(NGL_OPT_TRACE_WIDE) == 1))
     return batch_by_width(m0, B, any_blend, s);
   B.pause_at = pause;

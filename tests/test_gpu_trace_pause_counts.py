@@ -62,6 +62,13 @@ def test_second_count_not_above_the_first_is_ignored():
         assert lo <= n <= hi
 
 
+def test_short_traces_are_one_launch():
+    s = scene(96, 64)
+    for steps in (1, 2, 8, 24):
+        assert trace(*s, steps, 24)[1][1] == -1, steps
+    assert trace(*s, 25, 24)[1][1] == 0
+
+
 def test_late_pauses_of_a_batch():
     """Counts that the default no longer reaches on few rays give the single
     launch's outputs bit for bit."""
