@@ -537,7 +537,12 @@ __global__ __launch_bounds__(64 * NW) void k_normals_coop(ngl_model md, NormalAr
   // Groups of 64 points are dealt to the wavefronts of all blocks in turn,
   // starting seven blocks further in each round: an image's hits lie in bands
   // of rows and columns, so contiguous ranges, or the same column in every
-  // round, would leave many blocks idle.
+  // round, would leave many blocks idle.  Where one round takes all points, the
+  // groups that do not fill a block are the last block's: dealt too, they would
+  // make it as long as the others (65,537 points, 257 blocks on 256 CUs: 184 us
+  // against 157).
+  const int64_t groups = (P + 63) / 64;
+  const int64_t full = groups > int64_t(gridDim.x) * NW ? gridDim.x : groups < NW ? 1 : groups / NW;
   int64_t round = 0;
   for (;;) {
     // 1. queue active points until a full pass is available or the points
@@ -547,7 +552,8 @@ __global__ __launch_bounds__(64 * NW) void k_normals_coop(ngl_model md, NormalAr
     __syncthreads();
     while (n < NB && round * int64_t(gridDim.x) * NB < P) {
       const int64_t turn = round * NW + int64_t(threadIdx.x >> 6);
-      const int64_t p = (turn * gridDim.x + (blockIdx.x + 7 * turn) % gridDim.x) * 64 + int64_t(threadIdx.x & 63);
+      const int64_t group = blockIdx.x < full ? turn * full + (blockIdx.x + 7 * turn) % full : full * NW + turn;
+      const int64_t p = group * 64 + int64_t(threadIdx.x & 63);
       bool act = false;
       if (p < P) {
         act = A.status ? A.status[p] == NGL_RAY_HIT : true;
