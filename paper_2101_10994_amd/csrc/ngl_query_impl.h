@@ -721,11 +721,32 @@ struct QueryOp {
   }
 };
 
+// Whether query_sdf_all_lods takes a row of blocks per LOD or a lane per point.
+// Rows fill the chip with few points and decode on the matrix cores, but gather
+// every level again for each finer LOD.  Up to about 80,000 points rows are the
+// faster form at nearly every width (65,537 points of 5 LODs, time of a lane per
+// point = 1: M = 8, H = 32 0.90, 32 and 128 0.37, 64 and 256 0.94; not H = 16,
+// where M = 16 takes 1.28).  Beyond, they are where the decoder outweighs the
+// gather, H >= 64 and 2 M (2^18 points: 16 and 64 0.82, 32 and 64 0.80, 64 and 128
+// 0.70; against 8 and 32 1.43, 64 and 64 0.99, 1.13 at 2^19), blocks of four
+// wavefronts fit into the LDS (64 and 256: 1.10 to 1.33), and beyond 2^20 points,
+// M >= 32 and H >= 128 (2^22 points: 32 and 128 0.96, 32 and 64 1.15, 8 and 128
+// 1.17).
+template <int M, typename FT, class DEC>
+static bool all_lods_in_rows(const ngl_model& md, int64_t P) {
+  const int H = md.hidden;
+  if (P <= (H == 16 && M > 8 ? 40960 : 81920)) return true;
+  const size_t R = std::is_same<FT, F32>::value ? DEC::TILE_BYTES : tile_lds_bytes<DEC>(md.num_lods);
+  if (H < std::max(64, 2 * M) || DecLds<DEC>::fixed_bytes(H, false) + 4 * R > 65536) return false;
+  return P <= (1 << 20) || (M >= 32 && H >= 128);
+}
+
 template <int M, typename FT, bool XYZ>
 struct QueryAllOp {
   static int run(const ngl_model& md, const float* x, int64_t P, float* out, hipStream_t s) {
     // on the matrix cores: the row of LOD L is the query at LOD L, bit for bit
-    if (option(NGL_OPT_F32_DECODER) == 1 && option(NGL_OPT_COOP_GATHER) == 1)
+    if (option(NGL_OPT_F32_DECODER) == 1 && option(NGL_OPT_COOP_GATHER) == 1 &&
+        all_lods_in_rows<M, FT, DecF32All<M, XYZ>>(md, P))
       return launch_query_coop<M, FT, XYZ, DecF32All<M, XYZ>>(md, x, P, md.num_lods, 0.0f, nullptr, out, nullptr,
                                                               nullptr, s, md.num_lods);
     return launch_query_all<M, FT, XYZ>(md, x, P, out, s);
