@@ -35,6 +35,7 @@ constexpr int kSortGrid = 256;  // most blocks of the radix-sort passes
 constexpr int kDecGrid = 204;   // most blocks per LOD of the decoder-gradient pass (5 LODs fill 256 CUs x 4)
 constexpr int kFusedWaves = 8;  // wavefronts per block of k_dec_fused
 constexpr int kFusedGrid = 512; // most blocks of k_dec_fused
+constexpr int kCUs = 256;       // of the card: grids follow the batch alone, so that sums have the same bits everywhere
 
 // Grids sized to the batch (small batches of the fitting loop would
 // otherwise pay for the full grids): at least 1024 keys per sort block and
@@ -600,6 +601,10 @@ struct Fused {
   static constexpr int TRB = W2 + H;           // the scratch, and the sums after a LOD
   static constexpr int ACC = HT * CT * 4;      // accumulators of G per lane
   static constexpr int SUM = (ACC + 1) * 64;   // one wavefront's sums
+  // Blocks per CU that registers (and the LDS) allow: two with 128 registers a lane.
+  static constexpr int PER_CU = HT * CT <= 4 ? 2 : 1;
+  static constexpr int GRID = kCUs * PER_CU;
+  static_assert(GRID <= kFusedGrid, "partials of db2 and of the loss");
   static constexpr int FLOATS = TRB + std::max({NW * (WS + DS), NW / 2 * SUM, H * W});
 };
 
@@ -622,7 +627,7 @@ __device__ inline uint32_t mask2(uint32_t v, int i) {
 }
 
 template <int M, bool XYZ, int HT>
-__global__ __launch_bounds__(64 * kFusedWaves) void k_dec_fused(ngl_model md, FusedArgs F) {
+__global__ __launch_bounds__(64 * kFusedWaves, 2 * Fused<M, XYZ, HT>::PER_CU) void k_dec_fused(ngl_model md, FusedArgs F) {
   using S = Fused<M, XYZ, HT>;
   constexpr int NT = S::NT, CT = S::CT, NW = S::NW, DIN = S::DIN, OFF = S::OFF;
   __shared__ __align__(16) float sm[S::FLOATS];
@@ -1609,13 +1614,12 @@ static int check_train(const ngl_model* m) {
   return NGL_OK;
 }
 
-// Launches k_dec_fused with one round of resident blocks at most; returns the
-// blocks per LOD.
+// Launches k_dec_fused with one round of resident blocks of the whole card at
+// most; returns the blocks per LOD.
 template <int M, bool XYZ, int HT>
 static int launch_fused_h(const ngl_model& md, const FusedArgs& F, hipStream_t s) {
   const int threads = 64 * kFusedWaves;
-  int64_t grid = resident_grid(reinterpret_cast<const void*>(&k_dec_fused<M, XYZ, HT>), threads, 0, 0);
-  grid = std::min(grid, std::min<int64_t>(kFusedGrid, F.slots));
+  int64_t grid = std::min<int64_t>(Fused<M, XYZ, HT>::GRID, F.slots);
   const int rows = fused_rows(F.A.P) ? md.num_lods : 1;
   grid = std::max<int64_t>(1, std::min(grid / rows, (F.A.P + 16 * kFusedWaves - 1) / (16 * kFusedWaves)));
   k_dec_fused<M, XYZ, HT><<<dim3(unsigned(grid), unsigned(rows)), threads, 0, s>>>(md, F);
