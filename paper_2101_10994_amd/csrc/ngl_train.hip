@@ -602,7 +602,7 @@ struct Fused {
   static constexpr int ACC = HT * CT * 4;      // accumulators of G per lane
   static constexpr int SUM = (ACC + 1) * 64;   // one wavefront's sums
   // Blocks per CU that registers (and the LDS) allow: two with 128 registers a lane.
-  static constexpr int PER_CU = HT * CT <= 4 ? 2 : 1;
+  static constexpr int PER_CU = HT * CT <= 2 ? 2 : 1;
   static constexpr int GRID = kCUs * PER_CU;
   static_assert(GRID <= kFusedGrid, "partials of db2 and of the loss");
   static constexpr int FLOATS = TRB + std::max({NW * (WS + DS), NW / 2 * SUM, H * W});
@@ -627,7 +627,7 @@ __device__ inline uint32_t mask2(uint32_t v, int i) {
 }
 
 template <int M, bool XYZ, int HT>
-__global__ __launch_bounds__(64 * kFusedWaves, 2 * Fused<M, XYZ, HT>::PER_CU) void k_dec_fused(ngl_model md, FusedArgs F) {
+__global__ __launch_bounds__(64 * kFusedWaves, (2 * Fused<M, XYZ, HT>::PER_CU)) void k_dec_fused(ngl_model md, FusedArgs F) {
   using S = Fused<M, XYZ, HT>;
   constexpr int NT = S::NT, CT = S::CT, NW = S::NW, DIN = S::DIN, OFF = S::OFF;
   __shared__ __align__(16) float sm[S::FLOATS];
