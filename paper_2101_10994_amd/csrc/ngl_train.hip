@@ -1428,10 +1428,10 @@ __global__ __launch_bounds__(64) void k_rec_write(ngl_model md, FeatArgs A) {
 }
 
 // Sum of each voxel's records (ascending record order), one wavefront per
-// voxel of every level.
+// voxel of every level, from voxel g0 on.
 template <int M>
-__global__ __launch_bounds__(kBlock) void k_vox_reduce(FeatArgs A) {
-  const int64_t g = int64_t(blockIdx.x) * (kBlock / 64) + (threadIdx.x >> 6);
+__global__ __launch_bounds__(kBlock) void k_vox_reduce(FeatArgs A, int64_t g0) {
+  const int64_t g = g0 + int64_t(blockIdx.x) * (kBlock / 64) + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   if (g >= A.vox_off[A.Lm]) return;
   const int l = level_of(A.vox_off, A.Lm, g);
@@ -1769,7 +1769,12 @@ static int run_train(const ngl_model& md, const float* x, const float* target, c
     k_scan_inplace<<<Lm, 1024, 0, s>>>(w.rec_cnt, w.ntiles, w.rec_total, w.cnt_stride);
     if (P < kPointWaveMax || (fused && fused_rows(P))) k_rec_write<M, true, false><<<tgrid, 64, 0, s>>>(md, C);
     else k_rec_write<M, false, false><<<tgrid, 64, 0, s>>>(md, C);
-    k_vox_reduce<M><<<unsigned((C.vox_off[Lm] + kBlock / 64 - 1) / (kBlock / 64)), kBlock, 0, s>>>(C);
+    // a launch has fewer than 2^32 threads, 64 per voxel
+    constexpr int64_t kVoxLaunch = int64_t(1) << 25;
+    for (int64_t g0 = 0; g0 < C.vox_off[Lm]; g0 += kVoxLaunch) {
+      const int64_t n = std::min(kVoxLaunch, C.vox_off[Lm] - g0);
+      k_vox_reduce<M><<<unsigned((n + kBlock / 64 - 1) / (kBlock / 64)), kBlock, 0, s>>>(C, g0);
+    }
     k_corner<M, false><<<cgrid, kBlock, 0, s>>>(C);
   }
   NGL_LAUNCHED();
