@@ -605,35 +605,24 @@ __device__ __forceinline__ gptr<P> uniform_ptr(const void* p) {
 // the group covers consecutive bytes (64 where the row is that wide).
 template <int M, typename FT>
 struct TileRows {
-  static constexpr int ES = std::is_same<FT, F32>::value ? 4 : 2;
-  static constexpr int D = M / 4;                             // feature elements per lane
-  static constexpr int EPL = D * ES >= 16 ? 16 / ES : D;      // of them consecutive, in one load
-  static constexpr int NLD = D / EPL;                         // loads per row and lane
-  static constexpr int W = EPL * ES / 4;                      // 32-bit words per load
+  static_assert(!std::is_same<FT, F32>::value, "rows of 16-bit features");
+  static constexpr int D = M / 4;              // feature elements per lane
+  static constexpr int EPL = D >= 8 ? 8 : D;   // of them consecutive, in one load
+  static constexpr int NLD = D / EPL;          // loads per row and lane
+  static constexpr int W = EPL / 2;            // 32-bit words per load
   typedef uint32_t Words __attribute__((ext_vector_type(W)));
   // four corners' slices, as stored
   struct Half {
     Words v[4][NLD];
   };
-  __device__ static uint32_t offset(int c, int g) { return uint32_t(c) * uint32_t(M * ES) + uint32_t(g * EPL * ES); }
+  __device__ static uint32_t offset(int c, int g) { return uint32_t(c) * uint32_t(2 * M) + uint32_t(g * 2 * EPL); }
   __device__ static void issue(Half& h, gptr<char> base, const int4 c, int g) {
     const int cs[4] = {c.x, c.y, c.z, c.w};
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const gptr<char> r = base + offset(cs[j], g);
 #pragma unroll
-      for (int q = 0; q < NLD; ++q) h.v[j][q] = *(gptr<Words>)(r + q * 4 * EPL * ES);
-    }
-  }
-  // from the LDS copy of level 1 (read as LDS, not through a generic address)
-  __device__ static void issue_lds(Half& h, const void* base, const int4 c, int g) {
-    typedef const __attribute__((address_space(3))) char* lptr;
-    const int cs[4] = {c.x, c.y, c.z, c.w};
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const lptr r = (lptr)(base) + offset(cs[j], g);
-#pragma unroll
-      for (int q = 0; q < NLD; ++q) h.v[j][q] = *(const __attribute__((address_space(3))) Words*)(r + q * 4 * EPL * ES);
+      for (int q = 0; q < NLD; ++q) h.v[j][q] = *(gptr<Words>)(r + q * 8 * EPL);
     }
   }
   // acc += w[j] * slice of corner j, corner by corner
@@ -645,15 +634,11 @@ struct TileRows {
 #pragma unroll
         for (int e = 0; e < W; ++e) {
           const uint32_t b = h.v[j][q][e];
-          if constexpr (ES == 4) {
-            acc[q * EPL + e] = fmaf(w[j], __uint_as_float(b), acc[q * EPL + e]);
-          } else {
-            const int i = q * EPL + 2 * e;
-            const float lo = std::is_same<FT, BF16>::value ? bf16_to_f32(b & 0xffffu) : f16_to_f32(b & 0xffffu);
-            const float hi = std::is_same<FT, BF16>::value ? bf16_to_f32(b >> 16) : f16_to_f32(b >> 16);
-            acc[i] = fmaf(w[j], lo, acc[i]);
-            acc[i + 1] = fmaf(w[j], hi, acc[i + 1]);
-          }
+          const int i = q * EPL + 2 * e;
+          const float lo = std::is_same<FT, BF16>::value ? bf16_to_f32(b & 0xffffu) : f16_to_f32(b & 0xffffu);
+          const float hi = std::is_same<FT, BF16>::value ? bf16_to_f32(b >> 16) : f16_to_f32(b >> 16);
+          acc[i] = fmaf(w[j], lo, acc[i]);
+          acc[i + 1] = fmaf(w[j], hi, acc[i + 1]);
         }
   }
   // the lane's accumulators into staging row r
@@ -788,11 +773,12 @@ struct PointOrder {
 };
 
 // One SDF evaluation of the wavefront's 64 points: the features of levels
-// 1..lod summed, decoder lod, and for the points with `mix` the Eq. 3 blend
-// (weight a) with decoder lod + 1 on the sum with level lod + 1.  Each lane
+// 1..lod summed, decoder lod, and with `blend` (the same in all lanes) the Eq. 3
+// blend (weight a) with decoder lod + 1 on the sum with level lod + 1.  Each lane
 // brings its point: position x, voxel per level (-1: absent, then so are the
 // finer ones), the packed cell at level Lc, and `ok`, whether its result is
-// used.  Every lane of the wavefront must call it.
+// used.  By `order` the used points come first.  Every lane of the wavefront must
+// call it.
 //
 // The tiles with a used point are taken in turn.  A tile's corner ids are
 // read by the group, two per lane, for all levels at once and while the
@@ -805,62 +791,48 @@ struct PointOrder {
 // -> 0.701 ms); with FP32 features the two sets take the kernel from three
 // wavefronts per SIMD to two or make it spill (2^20 queries 0.209 -> 0.228 and
 // 0.235 ms), and in the normal kernel it measured the same.  Levels that
-// none of the tile's points has are skipped.  Every element is accumulated
-// over the corners and levels in the order of interp_level.
-//
-// SEL: points may lack a level that their tile runs (queries); they load
-// voxel 0's rows there and keep their accumulator.  Without SEL the results
-// of such lanes are unused.
-template <int M, typename FT, class DEC, bool SEL, bool ORDERED>
+// none of the tile's points has are skipped; a point that lacks a level its tile
+// runs loads voxel 0's rows there and keeps its accumulator.  Every element is
+// accumulated over the corners and levels in the order of interp_level.
+template <int M, typename FT, class DEC>
 __device__ __forceinline__ float tile_eval(const ngl_model& md, const DecLds<DEC>& S, const float x[3], const int* vox,
-                                           uint32_t cell, bool ok, bool mix, float a, int lod, int Lc, float b2a,
-                                           float b2b, const void* l1s, bool l1,
-                                           PointOrder order = PointOrder{}) {
+                                           uint32_t cell, bool ok, bool blend, float a, int lod, int Lc, float b2a,
+                                           float b2b, PointOrder order) {
   using T = TileRows<M, FT>;
   constexpr int D = T::D;
   const int lane = threadIdx.x & 63, r = lane >> 2, g = lane & 3;
   const int H = md.hidden;
   typename DEC::Stage* rows = S.stage;
   int32_t* ids = reinterpret_cast<int32_t*>(S.stage);
-  uint64_t okm = __ballot(ok), mixm = __ballot(mix);
-  if (ORDERED) {
-    // by place: the used points come first, and all of them blend or none
-    okm = __popcll(okm) == 64 ? ~0ull : (1ull << __popcll(okm)) - 1ull;
-    mixm = mixm ? okm : 0ull;
-    if (mixm) a = __shfl(a, order.from, 64);
-    mix = (mixm >> lane) & 1ull;
-  }
+  const int tiles = (__popcll(__ballot(ok)) + 15) / 16;
+  const int top = blend ? lod + 1 : lod;
+  if (blend) a = __shfl(a, order.from, 64);  // the weight of the point at this lane's place
   float mine = 0.0f;
-  if (okm == 0) return mine;
+  if (tiles == 0) return mine;
   int2 idr[NGL_MAX_LODS];  // this lane's two corner ids per level of the next tile
   int next_n = 0;          // levels that tile runs
-  uint32_t next_have = 0;  // SEL: bit l set when the group's point has level l
+  uint32_t next_have = 0;  // bit l set when the group's point has level l
   auto fetch = [&](int t) {
-    const int q = ORDERED ? __shfl(order.from, 16 * t + r, 64) : 16 * t + r;
-    const int top = ((mixm >> (16 * t)) & 0xffffull) ? lod + 1 : lod;
+    const int q = __shfl(order.from, 16 * t + r, 64);
     next_n = 0;
     next_have = 0;
 #pragma unroll
     for (int l = 1; l <= NGL_MAX_LODS; ++l) {
       if (l > top) break;
-      const int vq = __shfl((ORDERED || l <= lod ? ok : mix) ? vox[l - 1] : -1, q, 64);
-      if (SEL) {
-        if (__ballot(vq >= 0) == 0) break;
-        next_have |= uint32_t(vq >= 0) << l;
-      }
+      const int vq = __shfl(ok ? vox[l - 1] : -1, q, 64);
+      if (__ballot(vq >= 0) == 0) break;
+      next_have |= uint32_t(vq >= 0) << l;
       next_n = l;
       typedef int32_t i32x2 __attribute__((ext_vector_type(2)));
       const i32x2 c = *(gptr<i32x2>)(uniform_ptr<int32_t>(md.corners[l - 1]) + size_t(vq >= 0 ? vq : 0) * 8 + 2 * g);
       idr[l - 1] = make_int2(c[0], c[1]);
     }
   };
-  int t = (__ffsll((unsigned long long)okm) - 1) >> 4;
-  fetch(t);
-  for (;;) {
-    const int q = ORDERED ? __shfl(order.from, 16 * t + r, 64) : 16 * t + r;
+  fetch(0);
+  for (int t = 0;;) {
+    const int q = __shfl(order.from, 16 * t + r, 64);
     const int n = next_n;
     const uint32_t have = next_have;
-    const bool mt = ((mixm >> (16 * t)) & 0xffffull) != 0;
     float xq[3];
 #pragma unroll
     for (int k = 0; k < 3; ++k) xq[k] = __shfl(x[k], q, 64);
@@ -884,7 +856,7 @@ __device__ __forceinline__ float tile_eval(const ngl_model& md, const DecLds<DEC
     };
     // acc += set h of level l (weights w), where the point has the level
     auto add = [&](const typename T::Half& h, const float* w, int l) {
-      if (!SEL || ((have >> l) & 1u)) T::add(h, w, acc);
+      if ((have >> l) & 1u) T::add(h, w, acc);
     };
     auto finish = [&](int l) {  // the pending rows of level l
       float w[8];
@@ -892,27 +864,15 @@ __device__ __forceinline__ float tile_eval(const ngl_model& md, const DecLds<DEC
       add(A, w, l);
       add(B, w + 4, l);
     };
-    const int l0 = l1_bytes<M, FT>() > 0 && l1 ? 2 : 1;  // first level read from memory
-    if (n >= l0) {
+    if (n >= 1) {
       int4 c0, c1;
-      corner_ids(l0, c0, c1);
-      const gptr<char> feat = uniform_ptr<char>(md.feat[l0 - 1]);
+      corner_ids(1, c0, c1);
+      const gptr<char> feat = uniform_ptr<char>(md.feat[0]);
       T::issue(A, feat, c0, g);
       T::issue(B, feat, c1, g);
     }
-    if (l1_bytes<M, FT>() > 0 && l0 == 2 && n >= 1) {
-      int4 c0, c1;
-      corner_ids(1, c0, c1);
-      float w[8];
-      level_weights(1, cell_at(cq, Lc, 1), xq, w);
-      typename T::Half h;
-      T::issue_lds(h, l1s, c0, g);
-      add(h, w, 1);
-      T::issue_lds(h, l1s, c1, g);
-      add(h, w + 4, 1);
-    }
 #pragma unroll 1
-    for (int l = l0; l < n; ++l) {
+    for (int l = 1; l < n; ++l) {
       int4 c0, c1;
       corner_ids(l + 1, c0, c1);
       const gptr<char> feat = uniform_ptr<char>(md.feat[l]);
@@ -925,30 +885,26 @@ __device__ __forceinline__ float tile_eval(const ngl_model& md, const DecLds<DEC
     }
     // level n is pending; it belongs to decoder lod unless it is level lod + 1
     const bool pend = n > lod;
-    if (!pend && n >= l0) finish(n);
+    if (!pend && n >= 1) finish(n);
     wave_lds_sync();  // the ids are read; the staging rows take their place
     T::template put<DEC>(rows, r, g, acc);
     if (g == 0) DEC::tile_rest(rows, r, xq);
     if (pend) finish(n);  // z_{L+1} = z_L + psi_{L+1}
-    const uint64_t later = t < 3 ? okm >> (16 * t + 16) : 0ull;
-    const int nt = later ? t + 1 + ((__ffsll((unsigned long long)later) - 1) >> 4) : 4;
-    if (nt < 4) fetch(nt);
+    if (t + 1 < tiles) fetch(t + 1);
     wave_lds_sync();
     float d = b2a + DEC::tile(S.frag0, S.w2s0, rows, H);
-    if (mt) {
+    if (blend) {
       wave_lds_sync();
       T::template put<DEC>(rows, r, g, acc);
       wave_lds_sync();
       const float d1 = b2b + DEC::tile(S.frag1, S.w2s1, rows, H);
-      if (mix) d = (1.0f - a) * d + a * d1;
+      d = (1.0f - a) * d + a * d1;
     }
     wave_lds_sync();
     if ((lane >> 4) == t) mine = d;  // lane 16 t + j owns point 16 t + j
-    if (nt >= 4) break;
-    t = nt;
+    if (++t >= tiles) break;
   }
-  return ORDERED ? __shfl(mine, order.rank, 64) : mine;
+  return __shfl(mine, order.rank, 64);
 }
-
 
 }  // namespace ngl

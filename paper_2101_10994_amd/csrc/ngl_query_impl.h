@@ -160,29 +160,11 @@ __global__ __launch_bounds__(64 * NW) void k_query_mfma(ngl_model md, const floa
   }
 }
 
-// Cooperative gather: lanes locate their own points as above, then the
-// wavefront gathers and decodes its 64 points one 16-point tile at a time
-// (TileShape): the 4 lanes of group r serve point r of the tile, lane g
-// loading the elements [g M/4, g M/4 + M/4) of every corner row, so a row
-// (32 to 256 bytes) is read by 4 lanes together where one lane per point
-// reads whole rows alone.  Every element is accumulated in the same order
-// as interp_level and the staged decoder rows hold the same values, so the
-// results are those of k_query_mfma bit for bit.  Only one tile's
-// accumulators and staging rows are live at a time.
-// One evaluation of the wavefront's located points: features of levels
-// 1..lod, the decoder lod, and with `blend` the Eq. 3 mix (weight a, this
-// lane's) with decoder lod+1 on z + the level lod+1 voxel vn.  rows: this
-// wavefront's 16 staging rows.  Every lane must call it.
-//
-// Points may be taken in another order than the lanes': with `order` set,
-// order.rank is this lane's place and order.from the lane whose point has
-// this lane's place.  Levels that no point of a tile has are skipped.
-// Order by how many levels a point has (voxels nest, so these are the
-// coarsest ones), most first, so that points in empty space share tiles
-// that skip the fine levels; lanes without a point come last.  2^20 FP32
-// queries, half of them uniform in the box (they have 2.7 of 5 levels on
-// average): 0.209 -> 0.187 ms; 2^22 blended queries of the 7-LOD 16-bit model
-// 0.829 -> 0.766 ms.
+// A wavefront's points by how many levels they have (voxels nest, so these are the
+// coarsest ones), most first, so that points in empty space share tiles that
+// skip the fine levels; lanes without a point come last.  2^20 FP32 queries, half
+// of them uniform in the box (they have 2.7 of 5 levels on average): 0.209 -> 0.187
+// ms; 2^22 blended queries of the 7-LOD 16-bit model 0.829 -> 0.766 ms.
 __device__ __forceinline__ PointOrder order_by_depth(const int* vox, int Lp, bool act) {
   const int lane = threadIdx.x & 63;
   const uint64_t below = (1ull << lane) - 1ull;
@@ -201,6 +183,22 @@ __device__ __forceinline__ PointOrder order_by_depth(const int* vox, int Lp, boo
   return {rank, __builtin_amdgcn_ds_permute(4 * rank, lane)};
 }
 
+// Cooperative gather: lanes locate their own points as above, then the
+// wavefront gathers and decodes its 64 points one 16-point tile at a time
+// (TileShape): the 4 lanes of group r serve point r of the tile, lane g
+// loading the elements [g M/4, g M/4 + M/4) of every corner row, so a row
+// (32 to 256 bytes) is read by 4 lanes together where one lane per point
+// reads whole rows alone.  Every element is accumulated in the same order
+// as interp_level and the staged decoder rows hold the same values, so the
+// results are those of k_query_mfma bit for bit.  Only one tile's
+// accumulators and staging rows are live at a time.
+//
+// One evaluation of the wavefront's located points: features of levels
+// 1..lod, the decoder lod, and with `blend` the Eq. 3 mix (weight a, this
+// lane's) with decoder lod+1 on z + the level lod+1 voxel vn.  ORDERED: the points
+// are taken in another order than the lanes', order.rank being this lane's place
+// and order.from the lane whose point has this lane's place.  Levels that no point
+// of a tile has are skipped.  Every lane must call it.
 template <int M, typename FT, class DEC, bool ORDERED>
 __device__ __forceinline__ float coop_eval(const ngl_model& md, const DecLds<DEC>& S, const float x[3],
                                            const int* vox, int cx, int cy, int cz, int vn, bool act, int lod, int Lp,
@@ -307,8 +305,7 @@ __global__ __launch_bounds__(64 * NW) void k_query_coop(ngl_model md, const floa
     if (P - base > 16) order = order_by_depth(vox, Lp, act);
     float out;
     if constexpr (STREAMED)
-      out = tile_eval<M, FT, DEC, true, true>(md, S, x, vox, pack_cell(cx, cy, cz), act, act && blend, a, lod, Lp, b2a,
-                                              b2b, l1s, l1, order);
+      out = tile_eval<M, FT, DEC>(md, S, x, vox, pack_cell(cx, cy, cz), act, blend, a, lod, Lp, b2a, b2b, order);
     else
       out = coop_eval<M, FT, DEC, true>(md, S, x, vox, cx, cy, cz, vn, act, lod, Lp, blend, a, b2a, b2b, l1s, l1, order);
     if (act) {
