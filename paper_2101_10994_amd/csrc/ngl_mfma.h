@@ -787,8 +787,8 @@ struct PointOrder {
 // set is added, the same corners of the next level are requested into it,
 // so at least half a level's rows are always in flight and a tile waits for
 // one dependent read (ids, then rows) instead of two per level.  Used for
-// queries over 16-bit features (2^22 blended queries of the 7-LOD model 0.766
-// -> 0.701 ms); with FP32 features the two sets take the kernel from three
+// queries over wide 16-bit features (2^22 blended queries of the 7-LOD model 0.766
+// -> 0.701 ms; narrow rows and few levels are faster level by level); with FP32 features the two sets take the kernel from three
 // wavefronts per SIMD to two or make it spill (2^20 queries 0.209 -> 0.228 and
 // 0.235 ms), and in the normal kernel it measured the same.  Levels that
 // none of the tile's points has are skipped; a point that lacks a level its tile

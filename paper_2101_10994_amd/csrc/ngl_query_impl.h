@@ -254,10 +254,10 @@ __device__ __forceinline__ float coop_eval(const ngl_model& md, const DecLds<DEC
   return ORDERED ? __shfl(mine, order.rank, 64) : mine;
 }
 
-// DecF32All: the grid's row y evaluates LOD y + 1 into sdf[y][P].  Each row
+// STREAMED: tile_eval instead of coop_eval.  DecF32All: the grid's row y evaluates LOD y + 1 into sdf[y][P].  Each row
 // gathers its own levels again, and still 65,537 points at 5 LODs take 86 us
 // against 235 with a lane per point walking the LODs (k_query_all).
-template <int M, typename FT, bool XYZ, int NW, class DEC>
+template <int M, typename FT, bool XYZ, int NW, class DEC, bool STREAMED>
 __global__ __launch_bounds__(64 * NW) void k_query_coop(ngl_model md, const float* __restrict__ xs, int64_t P,
                                                         int lod, float alpha, const float* __restrict__ alpha_pp,
                                                         float* __restrict__ sdf, uint8_t* __restrict__ valid,
@@ -269,7 +269,6 @@ __global__ __launch_bounds__(64 * NW) void k_query_coop(ngl_model md, const floa
   }
   const int H = md.hidden;
   const bool blend = alpha_pp != nullptr || alpha > 0.0f;
-  constexpr bool STREAMED = !std::is_same<FT, F32>::value;
   const int tile_bytes = STREAMED ? tile_lds_bytes<DEC>(blend ? lod + 1 : lod) : DEC::TILE_BYTES;
   DecLds<DEC> S(smem, H, blend, tile_bytes / 4);
   // level 1's table after the staging rows (when the launch reserved it)
@@ -299,10 +298,14 @@ __global__ __launch_bounds__(64 * NW) void k_query_coop(ngl_model md, const floa
       vlast = vn = -1;
     }
     const float a = act ? (alpha_pp ? alpha_pp[p] : alpha) : 0.0f;
-    // 16 points are one tile in any order: a point of 16-bit features takes 8.9 us
-    // instead of 10.0 without the ordering (m = 32, h = 128)
+    // 16 points are one tile in any order, and 32 gain less than the ordering takes: a
+    // point of 16-bit features takes 8.9 us instead of 10.0 without it (m = 32, h =
+    // 128), 32 points of a small model 7.65 instead of 7.86.  Of one or two levels
+    // there is little to skip: 2^20 points in order take 1 % to 10 % more at one
+    // level, at two 3 % less to 8 % more (2 % to 6 % less at m = 64), at five 0 % to
+    // 15 % less.
     PointOrder order{int(threadIdx.x & 63), int(threadIdx.x & 63)};
-    if (P - base > 16) order = order_by_depth(vox, Lp, act);
+    if (P - base > 32 && Lp >= (M >= 64 ? 2 : 3)) order = order_by_depth(vox, Lp, act);
     float out;
     if constexpr (STREAMED)
       out = tile_eval<M, FT, DEC>(md, S, x, vox, pack_cell(cx, cy, cz), act, blend, a, lod, Lp, b2a, b2b, order);
@@ -320,13 +323,13 @@ __global__ __launch_bounds__(64 * NW) void k_query_coop(ngl_model md, const floa
   }
 }
 
-template <int M, typename FT, bool XYZ, int NW, class DEC>
+template <int M, typename FT, bool XYZ, int NW, class DEC, bool STREAMED>
 static int launch_query_coop_nw(const ngl_model& md, const float* x, int64_t P, int lod, float alpha,
                                 const float* app, float* sdf, uint8_t* valid, int32_t* vox, hipStream_t s,
                                 size_t lds, int rows) {
   // Grid-stride over the points with one round of resident blocks (each
   // stages the decoder once), or at most NGL_OPT_QUERY_BLOCKS_PER_CU per CU.
-  const void* kern = reinterpret_cast<const void*>(&k_query_coop<M, FT, XYZ, NW, DEC>);
+  const void* kern = reinterpret_cast<const void*>(&k_query_coop<M, FT, XYZ, NW, DEC, STREAMED>);
   const int bpc = option(NGL_OPT_QUERY_BLOCKS_PER_CU);
   int dev = 0, cus = 256;
   if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
@@ -337,23 +340,53 @@ static int launch_query_coop_nw(const ngl_model& md, const float* x, int64_t P, 
   int64_t grid = (P + 64 * NW - 1) / (64 * NW);
   const int64_t cap = bpc > 0 ? int64_t(cus) * bpc : resident_grid(kern, 64 * NW, lds, 0);
   if (grid > cap) grid = cap;
-  k_query_coop<M, FT, XYZ, NW, DEC><<<dim3(unsigned(grid), unsigned(rows)), 64 * NW, lds, s>>>(
+  k_query_coop<M, FT, XYZ, NW, DEC, STREAMED><<<dim3(unsigned(grid), unsigned(rows)), 64 * NW, lds, s>>>(
       md, x, P, lod, alpha, app, sdf, valid, vox, l1);
   NGL_LAUNCHED();
   return NGL_OK;
 }
 
+// Whether 16-bit rows are streamed (tile_eval): at m = 64, and at m = 32 from five
+// levels on.  Time of 2^18 and 2^20 points over FP16 features, discrete LODs, against
+// level by level: m = 64 0.91 and 0.99 at one level, 0.62 and 0.58 at five; m = 32 1.17
+// and 1.14 at one, 1.13 and 1.01 at four, 1.08 and 0.96 at five (0.97 of 257 and 5,000
+// points); m = 16 1.29 and 1.18 at one, 1.15 and 0.99 at five; m = 8 1.01 to 1.10.
+template <int M, typename FT>
+constexpr bool rows_streamed(int levels) {
+  return !std::is_same<FT, F32>::value && (M >= 64 || (M == 32 && levels >= 5));
+}
+template <int M, typename FT, class DEC>
+constexpr size_t query_tile_bytes(int levels) {
+  return rows_streamed<M, FT>(levels) ? tile_lds_bytes<DEC>(levels) : DEC::TILE_BYTES;
+}
+
+template <int M, typename FT, bool XYZ, class DEC, bool STREAMED>
+static int launch_query_coop_form(const ngl_model& md, const float* x, int64_t P, int lod, float alpha,
+                                  const float* app, float* sdf, uint8_t* valid, int32_t* vox, hipStream_t s, int rows) {
+  const bool blend = app != nullptr || alpha > 0.0f;
+  const size_t fixed = DecLds<DEC>::fixed_bytes(md.hidden, blend);
+  const size_t R = query_tile_bytes<M, FT, DEC>(blend ? lod + 1 : lod);
+  if (fixed + 4 * R <= 65536)
+    return launch_query_coop_nw<M, FT, XYZ, 4, DEC, STREAMED>(md, x, P, lod, alpha, app, sdf, valid, vox, s,
+                                                              fixed + 4 * R, rows);
+  if (fixed + 2 * R <= 65536)
+    return launch_query_coop_nw<M, FT, XYZ, 2, DEC, STREAMED>(md, x, P, lod, alpha, app, sdf, valid, vox, s,
+                                                              fixed + 2 * R, rows);
+  return launch_query_coop_nw<M, FT, XYZ, 1, DEC, STREAMED>(md, x, P, lod, alpha, app, sdf, valid, vox, s, fixed + R,
+                                                            rows);
+}
+
 template <int M, typename FT, bool XYZ, class DEC>
 static int launch_query_coop(const ngl_model& md, const float* x, int64_t P, int lod, float alpha, const float* app,
                              float* sdf, uint8_t* valid, int32_t* vox, hipStream_t s, int rows = 1) {
-  const bool blend = app != nullptr || alpha > 0.0f;
-  const size_t fixed = DecLds<DEC>::fixed_bytes(md.hidden, blend);
-  const size_t R = std::is_same<FT, F32>::value ? DEC::TILE_BYTES : tile_lds_bytes<DEC>(blend ? lod + 1 : lod);
-  if (fixed + 4 * R <= 65536)
-    return launch_query_coop_nw<M, FT, XYZ, 4, DEC>(md, x, P, lod, alpha, app, sdf, valid, vox, s, fixed + 4 * R, rows);
-  if (fixed + 2 * R <= 65536)
-    return launch_query_coop_nw<M, FT, XYZ, 2, DEC>(md, x, P, lod, alpha, app, sdf, valid, vox, s, fixed + 2 * R, rows);
-  return launch_query_coop_nw<M, FT, XYZ, 1, DEC>(md, x, P, lod, alpha, app, sdf, valid, vox, s, fixed + R, rows);
+  const bool streamed = rows_streamed<M, FT>(app != nullptr || alpha > 0.0f ? lod + 1 : lod);
+  if constexpr (rows_streamed<M, FT>(NGL_MAX_LODS)) {
+    if (streamed)
+      return launch_query_coop_form<M, FT, XYZ, DEC, true>(md, x, P, lod, alpha, app, sdf, valid, vox, s, rows);
+  }
+  if constexpr (!rows_streamed<M, FT>(1))
+    return launch_query_coop_form<M, FT, XYZ, DEC, false>(md, x, P, lod, alpha, app, sdf, valid, vox, s, rows);
+  return NGL_E_INVALID;  // not reached: one of the two forms
 }
 
 template <int M, typename FT, bool XYZ, int NW, class DEC>
@@ -733,7 +766,7 @@ template <int M, typename FT, class DEC>
 static bool all_lods_in_rows(const ngl_model& md, int64_t P) {
   const int H = md.hidden;
   if (P <= (H == 16 && M > 8 ? 40960 : 81920)) return true;
-  const size_t R = std::is_same<FT, F32>::value ? DEC::TILE_BYTES : tile_lds_bytes<DEC>(md.num_lods);
+  const size_t R = query_tile_bytes<M, FT, DEC>(md.num_lods);
   if (H < std::max(64, 2 * M) || DecLds<DEC>::fixed_bytes(H, false) + 4 * R > 65536) return false;
   return P <= (1 << 20) || (M >= 32 && H >= 128);
 }
