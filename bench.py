@@ -53,17 +53,17 @@ TRAVERSAL_BYTES = 16
 COUNTERS = {
     # both launches of the phased FP32 trace (first 24 evaluations, then the wide kernel)
     "k_sphere_trace": {"sources": ["ngl_trace_impl.h", "ngl_device.h", "ngl_mfma.h"],
-                       "sha256": "f3eea318163c0b52781a9996e82e8ca1242b8c3f5a5dbe11ab5de26d506966ef",
-                       "fetch_kib": 312591.9 + 22987.4, "write_kib": 33450.7 + 3516.8},
+                       "sha256": "f0951fe60af0daac7ecf4fd2a41c82b1c2aacd362923e55aea03508b5c32a221",
+                       "fetch_kib": 314995.8 + 23017.0, "write_kib": 33474.6 + 3520.2},
     # every launch of one traversal to depth 6 (root and six child passes,
     # ray inverses, segment offsets)
     "traverse": {"sources": ["ngl_traverse.hip", "ngl_device.h"],
-                 "sha256": "d1c4196cc585dd988bfdc7542ad8170f78014f558a7bdd22b721f7c9ab6091b1",
-                 "fetch_kib": 348071.9, "write_kib": 380740.2},
+                 "sha256": "324da1846f9f72260ce6e4d68263d36d2fe778ce4f423e3e2e4ea6b18adb1bcd",
+                 "fetch_kib": 348402.1, "write_kib": 380744.5},
     # k_query_coop, FP32 features and matrix-core decoder
     "k_query": {"sources": ["ngl_query_impl.h", "ngl_device.h", "ngl_mfma.h"],
-                "sha256": "3cfbe96b6ca4fb74ed93a90f236ee5dcc1c33da45d08b2c9b227385948328b9c",
-                "fetch_kib": 105003.0, "write_kib": 4096.0},
+                "sha256": "abe3214dc61f7eba1072426a504526b154112fc09dae74ae7ffecc49cb8d2911",
+                "fetch_kib": 105029.0, "write_kib": 4096.0},
 }
 FETCH_SCALE = (256 << 10) / 131087.9
 WRITE_SCALE = (256 << 10) / 262144.0

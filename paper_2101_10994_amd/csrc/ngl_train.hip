@@ -49,17 +49,20 @@ constexpr int kTile = 64;       // sorted points per record tile (one wavefront)
 // idle and each lane's serial decoder work would set the step time.
 constexpr int64_t kPointWaveMax = 16384;
 // From this many points on k_dec_fused takes the decoders of the widths it is
-// made for.  A step of 512 points, 5 LODs, M = 32, H = 128 takes 67 us with
-// k_point_wave and 68 with it, of 1,024 78 and 74, of 4,096 176 and 119, of
-// 16,383 403 and 161; at M = 8, H = 32 the two meet there as well.
+// made for.  A step of 1,023 points with k_point_wave and of 1,024 with it: 5 LODs,
+// M = 32, H = 128 78 and 79 us, M = 32, H = 32 69 and 65, M = 8, H = 32 56 and 54; one
+// LOD, M = 32, H = 128 61 and 69.  Of 4,096 points (5 LODs, 32, 128) 176 and 124, of
+// 16,383 403 and 166.
 constexpr int64_t kFusedMin = 1024;
 inline bool fused_widths(int M, int H) { return M <= 32 && (H == 32 || H == 64 || H == 128); }
 // Up to this many points k_dec_fused gives each LOD a row of blocks instead of
 // having every block do all LODs in turn: a block's decoder is loaded and its
 // sums are added up once instead of for every LOD (14 us each time, against
 // 6 us per tile of a wavefront), and k_rec_write adds the LODs' rows, which up
-// to here mostly come from the caches: a step of 65,537 points takes 249 us
-// instead of 307, of 262,144 584 instead of 602, of 393,216 796 instead of 773.
+// to here mostly come from the caches: a step of 65,537 points took 249 us
+// instead of 307, of 262,144 584 instead of 602, of 393,216 796 instead of 773
+// (with dw2 formed from G; now 262,144 points take 619 with rows, 262,145 658
+// without).
 constexpr int64_t kFusedRowsMax = 262144;
 inline bool fused_rows(int64_t P) { return P <= kFusedRowsMax; }
 // Batches up to this many points are sorted by ranks in one launch
@@ -558,13 +561,15 @@ __global__ __launch_bounds__(kBlock) void k_point_sums(ngl_model md, PointArgs A
 // only the small parts d2 go through C, and both are added by vector
 // instructions.  65,537 points, upstream gradients of mixed sign, db1 of five
 // LODs against FP64: median 3.7e-7 with one chain, 1.0e-7 with two, 3.0e-7 from
-// k_dec_grad; 2^19 points take 984 us a step instead of 974.  The masks are kept as bits: of
-// point j's units for the adjoint, and through LDS of a unit's points for G;
-// their BF16 value is 2, which is one bit, against g / 2.
+// k_dec_grad; 2^19 points take 984 us a step instead of 974.  The masks are kept
+// as bits: of point j's units for the adjoint, and through LDS of a unit's points
+// for G; their BF16 value is 2, which is one bit, against g / 2.
 // dW1 = w2 G and db1 = w2 G_1 are left to k_dec_reduce.  dw2 is the plain sum
 // of g relu(a), per lane in LDS (32 more registers are not there): as W1 G + b1
 // G_1 it would lose what cancels between the two, and take a point's NaN to every
 // unit (2^19 points 1023 us a step against 984 that way).
+// Products below 2^-100 lose low parts (BF16 parts become subnormal), and weights
+// are taken to be finite, w2 W1 in FP32's range too.
 // A wavefront runs its range of tiles for LOD after LOD from the finest down
 // and adds dpsi_{l+1}, which the same lane wrote, to dz_l.  The block shares
 // the decoder's fragments in LDS; each wavefront keeps its sums in registers,
@@ -572,7 +577,7 @@ __global__ __launch_bounds__(kBlock) void k_point_sums(ngl_model md, PointArgs A
 // Bound by the matrix instructions (2304 cycles per tile and LOD forward, 1088
 // for the rest at M = 32, H = 128) and about as much vector work beside the
 // FP32 ones, which does not overlap with them.  2^19 points, 5 LODs, M = 32,
-// H = 128: 569 us (764 with FP32 matrix instructions throughout), and 141 for
+// H = 128: 587 us (764 with FP32 matrix instructions throughout), and 138 for
 // the sums before it, against 1040 us for one lane per point (k_point) and 853
 // for the gradients (k_dec_grad).  Errors against FP64, median over four
 // widths, six sizes and six seeds, here and of those kernels: feature gradients
